@@ -287,6 +287,12 @@ NextSort next_sort(polyglot_ctx* ctx, const int32_t* windows, const int32_t* cor
   return nx;
 }
 
+// Where W1's fragments of the wide-layer path go.
+void large_frags(polyglot_ctx* ctx, LargeArgs* la) {
+  la->wf = reinterpret_cast<lu4*>(ctx->ws.wfrag);
+  la->wg = la->wf + (size_t)ctx->cfg.H * ctx->K * 6 / sizeof(lu4);
+}
+
 // The forward/backward launch(es), then (after `sorted_ev`, if any) the
 // table update and, for a list sorted as a whole, the long-segment fix-up of
 // one step, on the main stream; sorted mode reads sort set `set`.
@@ -324,7 +330,14 @@ int enqueue_compute(polyglot_ctx* ctx, float* E, float* W1, float* b1, float* w2
     la.c = ctx->c;
     la.B = B;
     la.invB = 1.0f / (float)B;
+    large_frags(ctx, &la);
+    la.slice = large_dw1_slice(cf.H, cf.d, cf.win, B);
+    la.n_slices = ceil_div(B, la.slice);
     {
+      Timed tm(ctx, POLYGLOT_K_FWDBWD);
+      e = launch_large_prep(la, tm.L);
+    }
+    if (e == hipSuccess) {
       Timed tm(ctx, POLYGLOT_K_FWDBWD);
       e = launch_large_fwd(la, 0, tm.L);
     }
@@ -415,10 +428,12 @@ int enqueue_compute(polyglot_ctx* ctx, float* E, float* W1, float* b1, float* w2
   aa.dn.loss_out = loss_dev ? loss_dev : ctx->ws.scratch_loss;
   aa.dn.part = ctx->ws.part;
   if (ctx->large) {  // dW1 slices; db1 / dw2 / loss partials of the forward workgroups
-    aa.dn.n_parts = ceil_div(B, kLgSlice);
-    aa.dn.part_stride = cf.H * ctx->K;
+    aa.dn.n_parts = la.n_slices;
+    aa.dn.part_stride = cf.H * (ctx->K + cf.d);
+    aa.dn.kx = cf.d;
+    aa.dn.c0 = ctx->c * cf.d;
     aa.dn.vpart = ctx->ws.vpart;
-    aa.dn.n_vparts = ceil_div(B, kLgRows);
+    aa.dn.n_vparts = large_fwd_grid(B);
     aa.dn.vstride = 2 * cf.H + 2;
   } else {
     aa.dn.n_parts = n_fb;
@@ -617,11 +632,20 @@ int polyglot_init(const polyglot_config* cfg, void* stream, polyglot_ctx** out) 
   }
   if (e == hipSuccess) e = alloc(ctx, &ws.G, (size_t)c.max_batch * (c.win + 1) * c.d);
   if (large) {
-    const int slices = ceil_div(c.max_batch, kLgSlice);
-    if (e == hipSuccess) e = alloc(ctx, &ws.part, (size_t)slices * c.H * ctx->K);
+    // at most one forward workgroup per CU, or one per 64 windows
+    const int slices = large_dw1_max_slices(c.H, c.d, c.win, c.max_batch);
+    const int fwd_wgs = std::min(ceil_div(c.max_batch, 16),
+                                 std::max(kCus, ceil_div(c.max_batch, 64)));
+    // one block: W1's fragments (2 layouts x 6 bytes), V, the dW1 slices (all
+    // multiples of 16 bytes), then the forward's partials
+    const size_t n_wf = (size_t)c.H * ctx->K * 3, n_v = (size_t)c.max_batch * 3 * c.H;
+    const size_t n_p = (size_t)slices * c.H * (ctx->K + c.d);
     if (e == hipSuccess)
-      e = alloc(ctx, &ws.vpart, (size_t)ceil_div(c.max_batch, kLgRows) * (2 * c.H + 2));
-    if (e == hipSuccess) e = alloc(ctx, &ws.vbuf, (size_t)c.max_batch * 3 * c.H);
+      e = alloc(ctx, &ws.vbuf, n_wf + n_v + n_p + (size_t)fwd_wgs * (2 * c.H + 2));
+    ws.wfrag = reinterpret_cast<uint32_t*>(ws.vbuf);
+    ws.vbuf += n_wf;
+    ws.part = ws.vbuf + n_v;
+    ws.vpart = ws.part + n_p;
   } else if (e == hipSuccess) {
     // two slots per tile group: the split backward gives each workgroup of a
     // pair its own
@@ -775,8 +799,15 @@ int polyglot_score(polyglot_ctx* ctx, const float* E, const float* W1, const flo
     la.K = ctx->K;
     la.c = ctx->c;
     la.B = B;
-    Timed tm(ctx, POLYGLOT_K_SCORE);
-    e = launch_large_fwd(la, 1, tm.L);
+    large_frags(ctx, &la);
+    {
+      Timed tm(ctx, POLYGLOT_K_SCORE);
+      e = launch_large_prep(la, tm.L);
+    }
+    if (e == hipSuccess) {
+      Timed tm(ctx, POLYGLOT_K_SCORE);
+      e = launch_large_fwd(la, 1, tm.L);
+    }
   } else {
     ScoreArgs a{E, W1, b1, w2, b2, windows, scores_dev, ctx->ws.flag, ctx->cfg.V, ctx->cfg.d,
                 ctx->cfg.win, ctx->cfg.H, ctx->K, B};

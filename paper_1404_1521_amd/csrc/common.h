@@ -19,6 +19,8 @@ constexpr int kMaxNT = kMaxHp / 16;
 constexpr int kMaxWin = 31;
 constexpr int kMaxD = 256;
 constexpr int kMaxLdsBytes = 160 * 1024;  // LDS per workgroup on gfx950
+constexpr int kXcds = 8;                  // compute dies, each with its own L2; blocks go round them
+constexpr int kCus = 256;
 
 // Radix sort of (row id, entry) pairs.
 constexpr int kSortTileKeys = 4096;                // multi-tile sort: keys per tile (long lists)
@@ -66,9 +68,10 @@ struct Workspace {
   // step
   float* G;                 // [max_batch*(win+1)][d] per-entry embedding gradients
   float* part;              // dense-gradient partials: [max_parts][part_stride], or
-                            // [slices][H][K] dW1 partials of the three-contraction path
+                            // [slices][H][K + d] dW1 partials of the three-contraction path
   float* vpart;             // three-contraction path: [forward workgroups][2H + 2]
   float* vbuf;              // three-contraction path: [max_batch][3][H] dz + dz~, dz, dz~
+  uint32_t* wfrag;          // three-contraction path: W1's MFMA fragments, [2][6 H K bytes]
   // segmented update
   float* seg_part;          // [ranges][2][seg_stride] partial sums of long segments (sized
                             // by chunks: at least the ranges of any call)

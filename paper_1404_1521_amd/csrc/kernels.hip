@@ -357,31 +357,58 @@ hipError_t launch_score(const ScoreArgs& a, int NT, int cpw, const Launch& L) {
   return launch_score_nt<4>(a, cpw, grid, lds, L);
 }
 
-hipError_t launch_large_fwd(const LargeArgs& a, int score_only, const Launch& L) {
-  const dim3 grid(ceil_div(a.B, kLgRows));
-  switch (a.H / 64) {
-    case 2: return pg_launch(k_large_fwd<2>, grid, dim3(2 * kWave), 0, L, a, score_only);
-    case 3: return pg_launch(k_large_fwd<3>, grid, dim3(3 * kWave), 0, L, a, score_only);
-    default: return pg_launch(k_large_fwd<4>, grid, dim3(4 * kWave), 0, L, a, score_only);
+hipError_t launch_large_prep(const LargeArgs& a, const Launch& L) {
+  return pg_launch(k_large_prep, dim3(ceil_div(2 * (a.H * a.K / 512), kWavesPerBlock)),
+                   dim3(kBlock), 0, L, a);
+}
+
+template <int NW, bool SCORE>
+static hipError_t launch_large_fwd_t(const LargeArgs& a, const Launch& L) {
+  const dim3 grid(large_fwd_grid(a.B)), block(NW * kWave);
+  switch (large_fwd_mt(a.B)) {
+    case 1: return pg_launch(k_large_fwd<NW, 1, SCORE>, grid, block, 0, L, a);
+    case 2: return pg_launch(k_large_fwd<NW, 2, SCORE>, grid, block, 0, L, a);
+    default: return pg_launch(k_large_fwd<NW, 4, SCORE>, grid, block, 0, L, a);
   }
 }
 
+hipError_t launch_large_fwd(const LargeArgs& a, int score_only, const Launch& L) {
+  switch (a.H / 64) {
+    case 2: return score_only ? launch_large_fwd_t<4, true>(a, L) : launch_large_fwd_t<4, false>(a, L);
+    case 3: return score_only ? launch_large_fwd_t<6, true>(a, L) : launch_large_fwd_t<6, false>(a, L);
+    default: return score_only ? launch_large_fwd_t<8, true>(a, L) : launch_large_fwd_t<8, false>(a, L);
+  }
+}
+
+template <int HW>
+static hipError_t launch_large_dw1_t(const LargeArgs& a, const Launch& L) {
+  const int cb = large_dw1_cols(a.d);
+  const int nwg = (a.K + a.d) / cb * a.n_slices;
+  const dim3 grid(ceil_div(nwg, kXcds) * kXcds);
+  const uint32_t lds = (uint32_t)large_dw1_lds(a.H, a.d, a.slice);
+  if (cb == 128)
+    return pg_launch(k_large_dw1<HW, 2>, grid, dim3(HW * 2 * kWave), lds, L, a);
+  return pg_launch(k_large_dw1<HW, 1>, grid, dim3(HW * kWave), lds, L, a);
+}
+
 hipError_t launch_large_dw1(const LargeArgs& a, const Launch& L) {
-  // 128-column blocks when they stay inside one window position
-  if (a.d % 128 == 0)
-    return pg_launch(k_large_dw1<128>, dim3(a.H / 64, a.K / 128, ceil_div(a.B, kLgSlice)),
-                     dim3(kBlock), 0, L, a);
-  return pg_launch(k_large_dw1<64>, dim3(a.H / 64, a.K / 64, ceil_div(a.B, kLgSlice)), dim3(kBlock),
-                   0, L, a);
+  switch (a.H / 64) {
+    case 2: return launch_large_dw1_t<2>(a, L);
+    case 3: return launch_large_dw1_t<3>(a, L);
+    default: return launch_large_dw1_t<4>(a, L);
+  }
 }
 
 hipError_t launch_large_g(const LargeArgs& a, const Launch& L) {
-  const dim3 grid(ceil_div(a.B, kLgGRows), a.win + 1);
-  switch (a.d / 16) {
-    case 4: return pg_launch(k_large_g<4>, grid, dim3(kBlock), 0, L, a);
-    case 8: return pg_launch(k_large_g<8>, grid, dim3(kBlock), 0, L, a);
-    case 12: return pg_launch(k_large_g<12>, grid, dim3(kBlock), 0, L, a);
-    default: return pg_launch(k_large_g<16>, grid, dim3(kBlock), 0, L, a);
+  // positions over several workgroups where the windows alone leave CUs idle
+  const int nx = ceil_div(a.B, kLgGRows);
+  const dim3 grid(nx, std::min(a.win + 1, std::max(1, kCus / nx)));
+  const uint32_t lds = (uint32_t)kLgGRows * a.H * 6;
+  switch (a.d / 64) {
+    case 1: return pg_launch(k_large_g<2, 4>, grid, dim3(8 * kWave), lds, L, a);
+    case 2: return pg_launch(k_large_g<4, 2>, grid, dim3(8 * kWave), lds, L, a);
+    case 3: return pg_launch(k_large_g<6, 1>, grid, dim3(6 * kWave), lds, L, a);
+    default: return pg_launch(k_large_g<8, 1>, grid, dim3(8 * kWave), lds, L, a);
   }
 }
 

@@ -1,210 +1,341 @@
 // The SGD step for models whose W1 does not fit in a workgroup's LDS (hidden
-// layer wider than 64 units, e.g. d 128, window 11, H 256): three MFMA
-// contractions (16x16x4 f32) with the embedding rows gathered on the fly.
+// layer wider than 64 units, e.g. d 128, window 11, H 256): three contractions
+// on the bfloat16 matrix instructions, each float32 operand split exactly
+// into three bfloat16 terms, with the embedding rows gathered on the fly.
 //
+//   k_large_prep  W1 split and laid out as MFMA operand fragments, once for
+//                 the forward (contraction over the window's columns) and once
+//                 for the rows G (contraction over the hidden units).
 //   k_large_fwd   Z = X W1^T and, for the corrupted copy, the centre-block
 //                 difference D = (e~ - e_c) W1_c^T (so z~ = z + D; §1 model,
 //                 x~); then tanh, both scores, hinge and the per-window
 //                 vectors V = (dz + dz~, dz, dz~), written to global memory,
-//                 and this workgroup's db1 / dw2 / loss partial.  32 windows
-//                 per workgroup, one wave per 64 hidden units.  In score-only
-//                 mode it writes s(x) instead.
-//   k_large_dw1   dW1 partials: dW1[h][k] = sum_b V_b[h] x_b[k] (centre block:
-//                 dz e_c + dz~ e~) over 1024-window slices; a workgroup owns a
-//                 64 x KT block of dW1 (KT = 128 when d allows, else 64) and
-//                 one slice, its operands staged through LDS.
+//                 and this workgroup's db1 / dw2 / loss partial.  In score-only
+//                 form it writes s(x) instead.
+//   k_large_dw1   dW1 partials: dW1[h][k] = sum_b V_b[h] x_b[k] over slices of
+//                 the batch (centre block: dz e_c, and in columns of its own
+//                 dz~ e~).
 //   k_large_g     G[e][:] = W1_j^T V for entry e = b(win+1) + j (context
 //                 positions dz + dz~, the true centre dz, the corrupt entry dz~
-//                 through block c); a workgroup owns 64 windows of one entry
-//                 position.
-// Rows b >= B read row 0 and are masked out of every result.
+//                 through block c).
+// Rows b >= B read row 0 (or zero) and are masked out of every result.
+//
+// The split.  x = x1 + x2 + x3, each term the leading 8 significant bits of
+// what is left (truncated, so no term overflows and the three hold all 24
+// bits).  Of the nine products the six of weight 2^-16 and more are kept; the
+// others are below 2^-24 of the product, a float32 rounding.  x1 y1 goes to an
+// accumulator of its own and the other five to a second one, so a contraction
+// rounds at the size of its sum once per 32 terms, where the float32
+// instruction rounds once per 4: against 64 bits the error of a 1408-term
+// contraction is 2.2e-7 of the result's norm, that of the float32 instruction
+// 6.7e-7 (320 terms: 1.0e-7 and 3.2e-7).  An infinite operand has finite
+// companions no more (inf - inf), which only the second accumulator sees: a
+// non-finite first sum is the result, as one float32 chain would give it.
+// Six bfloat16 products take 96 matrix cycles per 16x16x32 block, eight
+// float32 ones 256.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 #include "launch.h"
 
 namespace pg {
 
-__device__ __forceinline__ f4 lg_mfma(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+typedef __bf16 lb8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f4 lg_mfma(lu4 a, lu4 b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lb8, a),
+                                                 __builtin_bit_cast(lb8, b), c, 0, 0, 0);
 }
 
-// HW waves, wave w owns hidden units [64w, 64w + 64) (4 column blocks of 16);
-// both 16-row blocks of the workgroup's 32 windows.
-template <int HW>
-__global__ __launch_bounds__(HW * kWave) void k_large_fwd(LargeArgs a, int score_only) {
-  __shared__ int32_t ids[kLgRows][kMaxWin + 1];
-  __shared__ float sred[2][HW][kLgRows];
-  __shared__ float gsh[kLgRows];
-  __shared__ int badrow[kLgRows];
+// The three bfloat16 terms of eight floats, packed in order.
+__device__ __forceinline__ void lg_split8(const float (&x)[8], lu4 (&p)[3]) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    uint32_t u[2];
+    float r[2] = {x[2 * v], x[2 * v + 1]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        u[e] = __float_as_uint(r[e]);
+        r[e] = r[e] - __uint_as_float(u[e] & 0xffff0000u);
+      }
+      p[k][v] = __builtin_amdgcn_perm(u[1], u[0], 0x07060302u);  // both upper halves
+    }
+  }
+}
+
+// hi + lo, or hi alone where it is not finite.
+__device__ __forceinline__ f4 lg_sum(f4 hi, f4 lo) {
+  f4 r;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    r[q] = __builtin_fabsf(hi[q]) < __builtin_inff() ? hi[q] + lo[q] : hi[q];
+  return r;
+}
+
+// hi/lo[m][n] += A_m B[n] over one 32-term step, A_m's three fragments at
+// s + 192 m: row tiles in pairs, product-major, so that four accumulators
+// separate dependent instructions and few operand registers are live.
+template <int MT>
+__device__ __forceinline__ void lg_step(const lu4* s, const lu4 (&Bv)[2][3], f4 (&hi)[MT][2],
+                                        f4 (&lo)[MT][2]) {
+  constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};
+  constexpr int P = MT > 1 ? 2 : 1;
+#pragma unroll
+  for (int m = 0; m < MT; m += P) {
+    lu4 A[P][3];
+#pragma unroll
+    for (int v = 0; v < P; ++v)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) A[v][k] = s[((m + v) * 3 + k) * kWave];
+#pragma unroll
+    for (int p = 0; p < 5; ++p)
+#pragma unroll
+      for (int v = 0; v < P; ++v)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+          lo[m + v][n] = lg_mfma(A[v][PA[p]], Bv[n][PB[p]], lo[m + v][n]);
+#pragma unroll
+    for (int v = 0; v < P; ++v)
+#pragma unroll
+      for (int n = 0; n < 2; ++n) hi[m + v][n] = lg_mfma(A[v][0], Bv[n][0], hi[m + v][n]);
+  }
+}
+
+// =============================================================== W1 fragments
+//
+// A fragment is one operand of one MFMA: 64 lanes x 8 bfloat16 (16 bytes a
+// lane), lane (i, g) holding terms 8g..8g+7 of row i.
+//   wf[K/32 step][H/16 block][3 terms][64]  W1[16 hb + i][32 ks + 8g ..]
+//   wg[K/16 block][H/32 step][3 terms][64]  W1[32 hs + 8g ..][16 cb + i]
+// One wave per fragment triple; both layouts in one launch (the fragments of
+// wg follow those of wf).  4 us for H 256 x K 1408; without it every forward
+// and G workgroup would split W1 again (360,448 values, 256 times).
+__global__ __launch_bounds__(kBlock) void k_large_prep(LargeArgs a) {
+  const int t = threadIdx.x, lane = t & (kWave - 1);
+  const int i = lane & 15, g = lane >> 4;
+  const int n = a.H * a.K / 512;  // fragments of one layout
+  int u = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + t / kWave);
+  if (u >= 2 * n) return;
+  float x[8];
+  lu4* dst;
+  if (u < n) {
+    const int hb = u % (a.H / 16), ks = u / (a.H / 16);
+    const float* src = a.W1 + (size_t)(16 * hb + i) * a.K + 32 * ks + 8 * g;
+    const f4 v0 = ld4(src), v1 = ld4(src + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[e] = v0[e];
+      x[4 + e] = v1[e];
+    }
+    dst = a.wf + (size_t)u * 3 * kWave;
+  } else {
+    u -= n;
+    const int hs = u % (a.H / 32), cb = u / (a.H / 32);
+    const float* src = a.W1 + (size_t)(32 * hs + 8 * g) * a.K + 16 * cb + i;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = src[(size_t)e * a.K];
+    dst = a.wg + (size_t)u * 3 * kWave;
+  }
+  lu4 p[3];
+  lg_split8(x, p);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) dst[k * kWave + lane] = p[k];
+}
+
+// =============================================================== forward
+//
+// NW = H / 32 waves, wave w owning hidden units [32w, 32w + 32) of the
+// workgroup's 16 MT windows.  The windows' rows go through LDS in chunks of 64
+// columns as A fragments, double-buffered, the next chunk's rows in flight
+// in registers; W1's fragments belong to one wave each and come
+// straight from memory (the L2: every workgroup walks them in the same order),
+// one step ahead.  The centre block comes first, so that D's second
+// accumulator is gone before the other chunks.  Bound: the matrix
+// instructions, and for few windows the 6 H K bytes of fragments that every
+// workgroup reads, hence the smallest MT that needs at most one workgroup per
+// CU (large_fwd_mt).
+template <int NW, int MT, bool SCORE>
+__global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
+  constexpr int R = 16 * MT, NT = NW * kWave;
+  constexpr int UN = R * 8;                    // 8-column units of a chunk
+  constexpr int UPT = (UN + NT - 1) / NT;      // ... per thread
+  constexpr int SF = MT * 3 * kWave;           // fragment words of one step
+  __shared__ lu4 Xs[2][2 * SF];
+  __shared__ lu4 Ts[SCORE ? 1 : 2][SCORE ? 1 : 2 * SF];
+  __shared__ int32_t ids[R][kMaxWin + 1];
+  __shared__ float sred[2][NW][R];
+  __shared__ float gsh[R];
+  __shared__ int badrow[R];
   const int t = threadIdx.x, lane = t & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(t / kWave);
   const int i = lane & 15, g = lane >> 4;
-  const int r0 = blockIdx.x * kLgRows;
-  const int W1p = a.win + 1, d = a.d, K = a.K;
-  if (t < kLgRows) badrow[t] = 0;
+  const int r0 = blockIdx.x * R;
+  const int W1p = a.win + 1, d = a.d;
+  if (t < R) badrow[t] = 0;
   __syncthreads();
-  for (int k = t; k < kLgRows * W1p; k += HW * kWave) {
+  for (int k = t; k < R * W1p; k += NT) {
     const int r = k / W1p, j = k - r * W1p;
     const int b = r0 + r;
-    int32_t id = 0;  // score-only mode has no corrupt ids
-    if (b < a.B && (j < a.win || !score_only))
+    int32_t id = 0;  // the score has no corrupt ids
+    if (b < a.B && (j < a.win || !SCORE))
       id = j < a.win ? a.windows[(size_t)b * a.win + j] : a.corrupt[b];
     const bool bad = (uint32_t)id >= (uint32_t)a.V_rows;
     if (bad) {
       atomicOr(a.flag, kFlagBadId);
       badrow[r] = 1;
     }
-    ids[r][j] = ((uint32_t)id < (uint32_t)a.V_rows) ? id : 0;
+    ids[r][j] = bad ? 0 : id;
   }
   __syncthreads();
 
-  f4 Z[2][4], D[2][4];
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) Z[rb][cb] = D[rb][cb] = kZero4;
-  const int cpb = d / 16;  // 16-column chunks per embedding row
-  const int nch = K / 16;
-  // Chunk kc (16 columns of x) goes through LDS, row-major with 16-byte
-  // rows padded to 20 floats: Xs (the 32 windows' rows), Ts (the corrupt
-  // rows, centre block only) and Ws (W1 rows of all H units).  Lane (i, g)
-  // reads Xs[16rb+i][4g] and Ws[64w+16cb+i][4g] as float4: its operands of
-  // the four MFMAs (q) of the chunk.  The 256 float4 of Xs and Ts (item x:
-  // Xs for x < 128, else Ts; row (x&127)/4, column 4(x&3)) and the 64*HW*4
-  // float4 of Ws are spread over the workgroup's threads.
-  constexpr int NT = HW * kWave, XP = 20;
-  constexpr int XPT = (256 + NT - 1) / NT;  // float4 of Xs / Ts per thread
-  constexpr int WPT = (64 * HW * 4) / NT;   // float4 of W1 rows per thread (= 4)
-  __shared__ __align__(16) float Xs[2][kLgRows][XP];
-  __shared__ __align__(16) float Ts[2][kLgRows][XP];
-  __shared__ __align__(16) float Ws[2][64 * HW][XP];
-  auto load = [&](int kc, f4 (&Xv)[XPT], f4 (&Wv)[WPT]) {
-    const int jb = kc / cpb, off = (kc - jb * cpb) * 16;
-    const bool ctr = jb == a.c && !score_only;
-#pragma unroll
-    for (int u = 0; u < XPT; ++u) {
-      const int x = t + u * NT;
-      const int xr = (x & 127) / 4, xc = 4 * (x & 3);
-      if (x < 128) Xv[u] = ld4(a.E + (size_t)ids[xr][jb] * d + off + xc);
-      else if (x < 256 && ctr) Xv[u] = ld4(a.E + (size_t)ids[xr][a.win] * d + off + xc);
-    }
-#pragma unroll
-    for (int u = 0; u < WPT; ++u) {
-      const int x = t + u * NT;
-      Wv[u] = ld4(a.W1 + (size_t)(x / 4) * K + 16 * kc + 4 * (x & 3));
-    }
+  const int dch = d / 64, nch = a.K / 64, hb = a.H / 16;
+  // chunk q in the order of work: the centre block's, then the others
+  auto chunk_of = [&](int q) {
+    return q < dch ? a.c * dch + q : (q < (a.c + 1) * dch ? q - dch : q);
   };
-  auto store = [&](int buf, int kc, const f4 (&Xv)[XPT], const f4 (&Wv)[WPT]) {
-    const bool ctr = kc / cpb == a.c && !score_only;
+  f4 X[UPT][2], C[UPT][2];
+  // unit u of a chunk: row 16 (u / 128) + (u & 15), columns 32 ks + 8 g ..
+  auto load = [&](int q) {
+    const int kc = chunk_of(q), jb = kc / dch, off = (kc - jb * dch) * 64;
 #pragma unroll
-    for (int u = 0; u < XPT; ++u) {
-      const int x = t + u * NT;
-      const int xr = (x & 127) / 4, xc = 4 * (x & 3);
-      if (x < 128) st4(&Xs[buf][xr][xc], Xv[u]);
-      else if (x < 256 && ctr) st4(&Ts[buf][xr][xc], Xv[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < WPT; ++u) {
-      const int x = t + u * NT;
-      st4(&Ws[buf][x / 4][4 * (x & 3)], Wv[u]);
-    }
-  };
-  auto compute = [&](int buf, int kc) {
-    f4 A[2], Bv[4];
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) A[rb] = ld4(&Xs[buf][16 * rb + i][4 * g]);
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) Bv[cb] = ld4(&Ws[buf][64 * w + 16 * cb + i][4 * g]);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) Z[rb][cb] = lg_mfma(A[rb][q], Bv[cb][q], Z[rb][cb]);
-    if (kc / cpb == a.c && !score_only) {  // D = (e~ - e_c) W1_c^T
-      f4 At[2];
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb) At[rb] = ld4(&Ts[buf][16 * rb + i][4 * g]);
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-          const float dx = At[rb][q] - A[rb][q];
-#pragma unroll
-          for (int cb = 0; cb < 4; ++cb) D[rb][cb] = lg_mfma(dx, Bv[cb][q], D[rb][cb]);
+    for (int v = 0; v < UPT; ++v) {
+      const int u = t + v * NT;
+      if (u < UN) {
+        const int r = 16 * (u >> 7) + (u & 15), col = off + 32 * ((u >> 6) & 1) + 8 * ((u >> 4) & 3);
+        const float* src = a.E + (size_t)ids[r][jb] * d + col;
+        X[v][0] = ld4(src);
+        X[v][1] = ld4(src + 4);
+        if (!SCORE && q < dch) {
+          const float* sc = a.E + (size_t)ids[r][a.win] * d + col;
+          C[v][0] = ld4(sc);
+          C[v][1] = ld4(sc + 4);
         }
+      }
     }
   };
-  // two register sets: chunk kc+2 is loaded while chunks kc and kc+1 are
-  // contracted; one barrier per chunk (the buffer written at chunk kc was
-  // last read at chunk kc-2, before chunk kc-1's barrier)
-  f4 XA[XPT], WA[WPT], XB[XPT], WB[WPT];
+  auto store = [&](auto centre, int buf) {
 #pragma unroll
-  for (int u = 0; u < XPT; ++u) XA[u] = XB[u] = kZero4;
-  load(0, XA, WA);
-  if (nch > 1) load(1, XB, WB);
-  for (int kc = 0; kc < nch; kc += 2) {
-    store(0, kc, XA, WA);
-    if (kc + 2 < nch) load(kc + 2, XA, WA);
-    __syncthreads();
-    compute(0, kc);
-    if (kc + 1 >= nch) break;
-    store(1, kc + 1, XB, WB);
-    if (kc + 3 < nch) load(kc + 3, XB, WB);
-    __syncthreads();
-    compute(1, kc + 1);
-  }
-
-  // ---- epilogue.  Lane (i, g), component q of Z[rb][cb]: row 16rb + 4g + q,
-  // hidden 64w + 16cb + i.
-  float b1v[4], w2v[4];
+    for (int v = 0; v < UPT; ++v) {
+      const int u = t + v * NT;
+      if (u < UN) {
+        const int slot = (((u >> 6) & 1) * MT + (u >> 7)) * 3 * kWave + (u & 63);
+        float x[8];
+        lu4 p[3];
 #pragma unroll
-  for (int cb = 0; cb < 4; ++cb) {
-    const int h = 64 * w + 16 * cb + i;
-    b1v[cb] = h < a.H ? a.b1[h] : 0.f;
-    w2v[cb] = h < a.H ? a.w2[h] : 0.f;
-  }
-  float ps[2][4], pst[2][4];
+        for (int e = 0; e < 8; ++e) x[e] = X[v][e >> 2][e & 3];
+        lg_split8(x, p);
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
+        for (int k = 0; k < 3; ++k) Xs[buf][slot + k * kWave] = p[k];
+        if constexpr (decltype(centre)::value) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float s = 0.f, st = 0.f;
+          for (int e = 0; e < 8; ++e) x[e] = C[v][e >> 2][e & 3] - x[e];
+          lg_split8(x, p);
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        const float z = Z[rb][cb][q] + b1v[cb];
-        s += w2v[cb] * tanh_fast(z);
-        if (!score_only) st += w2v[cb] * tanh_fast(z + D[rb][cb][q]);
+          for (int k = 0; k < 3; ++k) Ts[buf][slot + k * kWave] = p[k];
+        }
       }
+    }
+  };
+  auto load_w = [&](int q, int ks, lu4 (&Bv)[2][3]) {
+    const lu4* src = a.wf + ((size_t)(2 * chunk_of(q) + ks) * hb + 2 * w) * 3 * kWave + lane;
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) Bv[n][k] = src[(n * 3 + k) * kWave];
+  };
+  f4 zh[MT][2], zl[MT][2], D[MT][2];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) zh[m][n] = zl[m][n] = D[m][n] = kZero4;
+  lu4 B0[2][3], B1[2][3];
+  load(0);
+  load_w(0, 0, B0);
+  load_w(0, 1, B1);
+  f4 dh[MT][2], dl[MT][2];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) dh[m][n] = dl[m][n] = kZero4;
+  // chunk q, in buffer q & 1: one barrier each (the buffer written at chunk q
+  // was last read at chunk q - 2, before chunk q - 1's barrier)
+  auto chunk = [&](auto centre, int q) {
+    const int buf = q & 1;
+    store(centre, buf);
+    if (q + 1 < nch) load(q + 1);
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      lu4 (&Bv)[2][3] = ks ? B1 : B0;
+      lg_step<MT>(&Xs[buf][ks * SF + lane], Bv, zh, zl);
+      if constexpr (decltype(centre)::value) lg_step<MT>(&Ts[buf][ks * SF + lane], Bv, dh, dl);
+      if (q + 1 < nch) load_w(q + 1, ks, Bv);
+    }
+  };
+  int q = 0;
+  if constexpr (!SCORE) {
+    for (; q < dch; ++q) chunk(std::true_type{}, q);
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < 2; ++n) D[m][n] = lg_sum(dh[m][n], dl[m][n]);
+  }
+  for (; q < nch; ++q) chunk(std::false_type{}, q);
+
+  // ---- epilogue.  Lane (i, g), component q of Z[m][n]: row 16m + 4g + q,
+  // hidden 32w + 16n + i.  Z becomes h, and ht holds h~.
+  float b1v[2], w2v[2];
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    b1v[n] = a.b1[32 * w + 16 * n + i];
+    w2v[n] = a.w2[32 * w + 16 * n + i];
+  }
+  f4 ht[MT][2];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    float s[4] = {0.f, 0.f, 0.f, 0.f}, st[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const f4 z = lg_sum(zh[m][n], zl[m][n]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float zb = z[c] + b1v[n];
+        zh[m][n][c] = tanh_fast(zb);
+        s[c] += w2v[n] * zh[m][n][c];
+        if (!SCORE) {
+          ht[m][n][c] = tanh_fast(zb + D[m][n][c]);
+          st[c] += w2v[n] * ht[m][n][c];
+        }
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
 #pragma unroll
       for (int o = 1; o < 16; o <<= 1) {
-        s += __shfl_xor(s, o);
-        st += __shfl_xor(st, o);
+        s[c] += __shfl_xor(s[c], o);
+        if (!SCORE) st[c] += __shfl_xor(st[c], o);
       }
-      ps[rb][q] = s;
-      pst[rb][q] = st;
+      if (i == 0) {
+        sred[0][w][16 * m + 4 * g + c] = s[c];
+        if (!SCORE) sred[1][w][16 * m + 4 * g + c] = st[c];
+      }
     }
-  if (i == 0) {
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        sred[0][w][16 * rb + 4 * g + q] = ps[rb][q];
-        sred[1][w][16 * rb + 4 * g + q] = pst[rb][q];
-      }
   }
   __syncthreads();
   float lossr = 0.f;
-  if (t < kLgRows) {
+  if (t < R) {
     float s = 0.f, st = 0.f;
 #pragma unroll
-    for (int v = 0; v < HW; ++v) {
+    for (int v = 0; v < NW; ++v) {
       s += sred[0][v][t];
-      st += sred[1][v][t];
+      if (!SCORE) st += sred[1][v][t];
     }
     const int b = r0 + t;
     const float b2v = a.b2[0];
-    if (score_only) {
+    if (SCORE) {
       if (b < a.B) a.scores[b] = badrow[t] ? __builtin_nanf("") : b2v + s;
     } else {
       const float mg = 1.f - (b2v + s) + (b2v + st);
@@ -213,53 +344,50 @@ __global__ __launch_bounds__(HW * kWave) void k_large_fwd(LargeArgs a, int score
       lossr = on ? mg : 0.f;
     }
   }
-  if (score_only) return;
+  if (SCORE) return;
   __syncthreads();
 
-  // V and the db1 / dw2 sums of this lane's hidden units over its 8 rows
-  float db1[4] = {0.f, 0.f, 0.f, 0.f}, dw2[4] = {0.f, 0.f, 0.f, 0.f};
+  // V and the db1 / dw2 sums of this lane's hidden units over its rows
+  float db1[2] = {0.f, 0.f}, dw2[2] = {0.f, 0.f};
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = 16 * rb + 4 * g + q, b = r0 + r;
+    for (int c = 0; c < 4; ++c) {
+      const int r = 16 * m + 4 * g + c, b = r0 + r;
       const float gst = gsh[r];
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        const int h = 64 * w + 16 * cb + i;
-        const float z = Z[rb][cb][q] + b1v[cb];
-        const float hh = tanh_fast(z), ht = tanh_fast(z + D[rb][cb][q]);
+      for (int n = 0; n < 2; ++n) {
+        const float hh = zh[m][n][c], hc = ht[m][n][c];
         // h - h~ = tanh(z - z~) (1 - h h~) with z - z~ = -D
-        const float hmh = tanh_fast(-D[rb][cb][q]) * (1.f - hh * ht);
-        const float gw = gst * w2v[cb];
+        const float hmh = tanh_fast(-D[m][n][c]) * (1.f - hh * hc);
+        const float gw = gst * w2v[n];
         const float dz = -gw * (1.f - hh * hh);
-        const float dzt = gw * (1.f - ht * ht);
-        const float dsum = gw * hmh * (hh + ht);
-        if (b < a.B && h < a.H) {
-          float* vr = a.V + (size_t)b * 3 * a.H + h;
+        const float dzt = gw * (1.f - hc * hc);
+        const float dsum = gw * hmh * (hh + hc);
+        if (b < a.B) {
+          float* vr = a.V + (size_t)b * 3 * a.H + 32 * w + 16 * n + i;
           vr[0] = dsum;
           vr[a.H] = dz;
           vr[2 * a.H] = dzt;
         }
-        db1[cb] += dsum;
-        dw2[cb] -= gst * hmh;  // -(m/B) h + (m/B) h~
+        db1[n] += dsum;
+        dw2[n] -= gst * hmh;  // -(m/B) h + (m/B) h~
       }
     }
   float* vp = a.vpart + (size_t)blockIdx.x * (2 * a.H + 2);
 #pragma unroll
-  for (int cb = 0; cb < 4; ++cb) {
-    float x = db1[cb], y = dw2[cb];
+  for (int n = 0; n < 2; ++n) {
+    float x = db1[n], y = dw2[n];
     x += __shfl_xor(x, 16);
     x += __shfl_xor(x, 32);
     y += __shfl_xor(y, 16);
     y += __shfl_xor(y, 32);
-    const int h = 64 * w + 16 * cb + i;
-    if (g == 0 && h < a.H) {
-      vp[h] = x;
-      vp[a.H + h] = y;
+    if (g == 0) {
+      vp[32 * w + 16 * n + i] = x;
+      vp[a.H + 32 * w + 16 * n + i] = y;
     }
   }
-  if (w == 0) {  // the workgroup's hinge sum (rows in order), db2 = 0
+  if (w == 0) {  // the workgroup's hinge sum (rows in order; R <= 64), db2 = 0
     for (int o = 1; o < kWave; o <<= 1) lossr += __shfl_xor(lossr, o);
     if (lane == 0) {
       vp[2 * a.H] = lossr;
@@ -268,202 +396,264 @@ __global__ __launch_bounds__(HW * kWave) void k_large_fwd(LargeArgs a, int score
   }
 }
 
-// dW1 partial of a 64 x KT block (hidden h0.., columns k0.. inside one
-// window position j) over one 1024-window slice.  The operands go through
-// LDS in 16-window blocks, row-major (one window per row):
-//   Vs[w][h]   = the window's vector for this position (dz + dz~ for a
-//                context position; dz, then dz~ in a second phase, for the
-//                centre, whose rows are the true centre and the corrupt word)
-//   Xs[w][col] = E[id(w, j)][off0 + col]
-// MFMA q of a block contracts windows {q, 4+q, 8+q, 12+q}: lane (i, g)
-// supplies Vs[4g+q][16rt+i] and Xs[4g+q][16ct+i].  Row strides are 4 mod 8
-// floats, so the two row groups a half-wave reads sit on disjoint banks,
-// and a row is stored with float4 writes.  Wave w owns columns
-// [w*KT/4, (w+1)*KT/4) and all 64 hidden rows.  The slice's row ids are
-// staged in LDS first; rows two blocks ahead are in flight in registers.
-template <int KT>
-__global__ __launch_bounds__(kBlock) void k_large_dw1(LargeArgs a) {
-  constexpr int CT = KT / 64;          // 16-column tiles per wave
-  constexpr int XF = 16 * KT / 4;      // float4 of one block's rows
-  constexpr int XPT = XF / kBlock;     // ... per thread
-  constexpr int XS = KT + 4, VS = 64 + 4;
-  __shared__ __align__(16) float Vs[2][16][VS];
-  __shared__ __align__(16) float Xs[2][16][XS];
-  __shared__ int32_t ids_s[2][kLgSlice];  // row ids of the slice, per phase
+// =============================================================== dW1
+//
+// One workgroup per (64 CW columns of one window position or of the corrupt
+// row, slice of the batch), all H = 64 HW hidden units; wave (wh, wc) owns a
+// 64 x 64 block.  The contraction runs over the slice's windows, 32 a step:
+// both operands need eight windows of one column per lane, so a thread reads
+// a column of eight rows (adjacent threads, adjacent columns), splits it and
+// stores whole fragments.  The next step's values are in flight in registers
+// during a step.  The centre's true and corrupt halves are columns of their
+// own (partial columns K .. K + d), so that every workgroup has the same
+// work, and the slices are cut so that the workgroups fill the CUs once
+// (large_dw1_slice).  Workgroups of one slice share its vectors: consecutive
+// ones of the list go to one XCD (blocks go round the XCDs).
+template <int HW, int CW>
+__global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
+  constexpr int H = 64 * HW, CB = 64 * CW, NT = HW * CW * kWave;
+  constexpr int VU = H * 4 / NT;                  // V units (a column of 8 windows) per thread
+  constexpr int XU = (CB * 4 + NT - 1) / NT;      // X units per thread
+  constexpr int VF = (H / 16) * 3 * kWave, XF = (CB / 16) * 3 * kWave;
+  extern __shared__ lu4 lds_q[];
+  lu4* Vs = lds_q;                                // [2][VF]
+  lu4* Xs = lds_q + 2 * VF;                       // [2][XF]
+  int32_t* ids = reinterpret_cast<int32_t*>(Xs + 2 * XF);  // [slice]
   const int t = threadIdx.x, lane = t & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(t / kWave);
-  const int i = lane & 15, g = lane >> 4;
-  const int h0 = blockIdx.x * 64, k0 = blockIdx.y * KT, sl = blockIdx.z;
-  const int d = a.d, j = k0 / d, off0 = k0 - j * d;
-  const int phases = (j == a.c) ? 2 : 1;
-  const int b_lo = sl * kLgSlice, b_hi = min(a.B, b_lo + kLgSlice), nb = b_hi - b_lo;
-  const int nblk = (nb + 15) / 16, total = phases * nblk;
+  const int wh = w % HW, wc = w / HW;
+  const int d = a.d, ncol = (a.K + d) / CB, nwg = ncol * a.n_slices;
+  const int per = (nwg + kXcds - 1) / kXcds;
+  const int f = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+  if ((int)(blockIdx.x / kXcds) >= per || f >= nwg) return;
+  const int sl = f / ncol, k0 = (f - sl * ncol) * CB;
+  const int j = k0 / d, off0 = k0 - j * d;  // j == win: the corrupt row
+  const int ty = j == a.win ? 2 : (j == a.c ? 1 : 0);
+  const int b_lo = sl * a.slice, nb = min(a.B - b_lo, a.slice);
+  const int steps = (nb + 31) / 32;
 
-  // every row id of the slice up front, so a block's row loads depend on LDS only
-  for (int x = t; x < nb; x += kBlock) {
-    const int32_t id0 = a.windows[(size_t)(b_lo + x) * a.win + j];
-    ids_s[0][x] = (uint32_t)id0 < (uint32_t)a.V_rows ? id0 : 0;
-    if (phases == 2) {
-      const int32_t id1 = a.corrupt[b_lo + x];
-      ids_s[1][x] = (uint32_t)id1 < (uint32_t)a.V_rows ? id1 : 0;
-    }
+  for (int x = t; x < nb; x += NT) {
+    const int32_t id = j == a.win ? a.corrupt[b_lo + x] : a.windows[(size_t)(b_lo + x) * a.win + j];
+    ids[x] = (uint32_t)id < (uint32_t)a.V_rows ? id : 0;
   }
   __syncthreads();
 
-  // this thread's share of a block: XPT float4 of rows (window xw[u], float4
-  // column xc), one float4 of vectors (window t/16, hidden 4*(t%16))
-  const int xc = t % (KT / 4);
-  int xw[XPT];
+  const float* vbase = a.V + (size_t)b_lo * 3 * H + (size_t)ty * H;
+  float vr[VU][8], xr[XU][8];
+  auto load = [&](int st) {
 #pragma unroll
-  for (int u = 0; u < XPT; ++u) xw[u] = (t + u * kBlock) / (KT / 4);
-  const int vw = t / 16, vh = 4 * (t % 16);
-  auto load = [&](int bi, f4 (&X)[XPT], f4& Vv) {
-    const int ph = bi / nblk, r0 = (bi - ph * nblk) * 16;
-    const int slot = (phases == 1) ? 0 : 1 + ph;
+    for (int u = 0; u < VU; ++u) {
+      const int x = t + u * NT, h = x % H, r = 32 * st + 8 * (x / H);
 #pragma unroll
-    for (int u = 0; u < XPT; ++u) {
-      const int r = r0 + xw[u];
-      const int32_t id = r < nb ? ids_s[ph][r] : 0;
-      X[u] = ld4(a.E + (size_t)id * d + off0 + 4 * xc);
+      for (int e = 0; e < 8; ++e) vr[u][e] = r + e < nb ? vbase[(size_t)(r + e) * 3 * H + h] : 0.f;
     }
-    const int r = r0 + vw;
-    Vv = r < nb ? ld4(a.V + (size_t)(b_lo + r) * 3 * a.H + (size_t)slot * a.H + h0 + vh) : kZero4;
-  };
-  auto store = [&](int buf, const f4 (&X)[XPT], const f4& Vv) {
 #pragma unroll
-    for (int u = 0; u < XPT; ++u) st4(&Xs[buf][xw[u]][4 * xc], X[u]);
-    st4(&Vs[buf][vw][vh], Vv);
-  };
-  f4 acc[4][CT];
+    for (int u = 0; u < XU; ++u) {
+      const int x = t + u * NT, col = x % CB, r = 32 * st + 8 * (x / CB);
 #pragma unroll
-  for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = kZero4;
-  auto compute = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float A[4], Bm[CT];
-#pragma unroll
-      for (int rt = 0; rt < 4; ++rt) A[rt] = Vs[buf][4 * g + q][16 * rt + i];
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) Bm[ct] = Xs[buf][4 * g + q][16 * (w * CT + ct) + i];
-#pragma unroll
-      for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = lg_mfma(A[rt], Bm[ct], acc[rt][ct]);
+      for (int e = 0; e < 8; ++e)
+        xr[u][e] = x < CB * 4 && r + e < nb ? a.E[(size_t)ids[r + e] * d + off0 + col] : 0.f;
     }
   };
-
-  // two register sets: the rows of block bi+2 are loaded while blocks bi and
-  // bi+1 are contracted.  One barrier per block: the LDS buffer written at
-  // block bi was last read at block bi-2, before block bi-1's barrier.
-  f4 XA[XPT], VA, XB[XPT], VB;
-  if (total > 0) load(0, XA, VA);
-  if (total > 1) load(1, XB, VB);
-  for (int bi = 0; bi < total; bi += 2) {
-    store(0, XA, VA);
-    if (bi + 2 < total) load(bi + 2, XA, VA);
-    __syncthreads();
-    compute(0);
-    if (bi + 1 >= total) break;
-    store(1, XB, VB);
-    if (bi + 3 < total) load(bi + 3, XB, VB);
-    __syncthreads();
-    compute(1);
-  }
-  // lane (i, g), component r: hidden h0 + 16rt + 4g + r, column k0 + 16(w*CT + ct) + i
-  float* P = a.part + (size_t)sl * a.H * a.K;
+  auto store = [&](int buf) {
+    lu4 p[3];
 #pragma unroll
-  for (int rt = 0; rt < 4; ++rt)
+    for (int u = 0; u < VU; ++u) {
+      const int x = t + u * NT, h = x % H, gq = x / H;
+      lg_split8(vr[u], p);
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
+      for (int k = 0; k < 3; ++k)
+        Vs[buf * VF + ((h >> 4) * 3 + k) * kWave + 16 * gq + (h & 15)] = p[k];
+    }
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        P[(size_t)(h0 + 16 * rt + 4 * g + r) * a.K + k0 + 16 * (w * CT + ct) + i] = acc[rt][ct][r];
-}
-
-// G rows of 64 windows at entry position j = blockIdx.y:
-// G[b(win+1)+j][:] = W1_jj^T v_b (jj = c for the corrupt entry).  The
-// contraction over hidden units goes in 16-unit steps through LDS,
-// row-major: Vs[w][h] (the window's vector for this position) and
-// Ws[h][col] (W1 rows hc.. of column block jj).  MFMA q of a step contracts
-// units {q, 4+q, 8+q, 12+q}: lane (i, g) supplies Vs[16w'+i][4g+q] (one
-// 128-bit read for all four) and Ws[4g+q][16ct+i]; Ws rows are 4 mod 8
-// floats long, so a half-wave's two rows sit on disjoint banks.  Wave w'
-// owns windows 16w'.. and all DQ column blocks; the rows of step s+2 are in
-// flight in registers while steps s and s+1 are contracted.
-template <int DQ>
-__global__ __launch_bounds__(kBlock) void k_large_g(LargeArgs a) {
-  constexpr int D = 16 * DQ, WS = D + 4, VS = 16 + 4;
-  constexpr int WF = 16 * D / 4;                     // float4 of a step's W1 rows
-  constexpr int WPT = (WF + kBlock - 1) / kBlock;    // ... per thread
-  __shared__ __align__(16) float Vs[2][kLgGRows][VS];
-  __shared__ __align__(16) float Ws[2][16][WS];
-  const int t = threadIdx.x, lane = t & (kWave - 1);
-  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
-  const int i = lane & 15, g = lane >> 4;
-  const int j = blockIdx.y, b0 = blockIdx.x * kLgGRows;
-  const int ty = (j == a.win) ? 2 : (j == a.c ? 1 : 0);
-  const int jj = (j == a.win) ? a.c : j;
-  const int nsteps = a.H / 16;
-  // this thread's share of a step: one float4 of vectors (window t/4, units
-  // 4*(t%4)), WPT float4 of W1 rows (row x / (D/4), float4 column x % (D/4))
-  const int vw = t / 4, vh = 4 * (t % 4);
-  const bool vok = b0 + vw < a.B;
-  const float* vsrc = a.V + (size_t)(vok ? b0 + vw : 0) * 3 * a.H + (size_t)ty * a.H + vh;
-  auto load = [&](int st, f4& Vv, f4 (&Wv)[WPT]) {
-    const int hc = st * 16;
-    Vv = vok ? ld4(vsrc + hc) : kZero4;
+    for (int u = 0; u < XU; ++u) {
+      const int x = t + u * NT, col = x % CB, gq = x / CB;
+      if (x < CB * 4) {
+        lg_split8(xr[u], p);
 #pragma unroll
-    for (int u = 0; u < WPT; ++u) {
-      const int x = t + u * kBlock;
-      if (x < WF) {
-        const int r = x / (D / 4), c4 = x % (D / 4);
-        Wv[u] = ld4(a.W1 + (size_t)(hc + r) * a.K + (size_t)jj * D + 4 * c4);
+        for (int k = 0; k < 3; ++k)
+          Xs[buf * XF + ((col >> 4) * 3 + k) * kWave + 16 * gq + (col & 15)] = p[k];
       }
     }
   };
-  auto store = [&](int buf, const f4& Vv, const f4 (&Wv)[WPT]) {
-    st4(&Vs[buf][vw][vh], Vv);
+  f4 hi[4][4], lo[4][4];
 #pragma unroll
-    for (int u = 0; u < WPT; ++u) {
-      const int x = t + u * kBlock;
-      if (x < WF) st4(&Ws[buf][x / (D / 4)][4 * (x % (D / 4))], Wv[u]);
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int n = 0; n < 4; ++n) hi[m][n] = lo[m][n] = kZero4;
+  load(0);
+  store(0);
+  if (steps > 1) load(1);
+  __syncthreads();
+  // step st reads buffer st & 1 and fills the other one, last read at step
+  // st - 1, before its closing barrier
+  for (int st = 0; st < steps; ++st) {
+    const int buf = st & 1;
+    if (st + 1 < steps) store(buf ^ 1);
+    if (st + 2 < steps) load(st + 2);
+    const lu4* vs = Vs + buf * VF + wh * 4 * 3 * kWave + lane;
+    const lu4* xs = Xs + buf * XF + wc * 4 * 3 * kWave + lane;
+    lu4 A[4][3];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) A[m][k] = vs[(m * 3 + k) * kWave];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      lu4 Bv[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) Bv[k] = xs[(n * 3 + k) * kWave];
+      constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+      for (int p = 0; p < 5; ++p)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) lo[m][n] = lg_mfma(A[m][PA[p]], Bv[PB[p]], lo[m][n]);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) hi[m][n] = lg_mfma(A[m][0], Bv[0], hi[m][n]);
     }
-  };
-  f4 acc[DQ];
-#pragma unroll
-  for (int ct = 0; ct < DQ; ++ct) acc[ct] = kZero4;
-  auto compute = [&](int buf) {
-    const f4 av = ld4(&Vs[buf][16 * w + i][4 * g]);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int ct = 0; ct < DQ; ++ct) acc[ct] = lg_mfma(av[q], Ws[buf][4 * g + q][16 * ct + i], acc[ct]);
-  };
-  f4 VA, WA[WPT], VB, WB[WPT];
-  load(0, VA, WA);
-  if (nsteps > 1) load(1, VB, WB);
-  for (int st = 0; st < nsteps; st += 2) {
-    store(0, VA, WA);
-    if (st + 2 < nsteps) load(st + 2, VA, WA);
     __syncthreads();
-    compute(0);
-    if (st + 1 >= nsteps) break;
-    store(1, VB, WB);
-    if (st + 3 < nsteps) load(st + 3, VB, WB);
-    __syncthreads();
-    compute(1);
   }
-  // lane (i, g), component q: window b0 + 16w + 4g + q, column 16ct + i
+  // lane (i, g), component r: hidden 64 wh + 16m + 4g + r, column k0 + 64 wc + 16n + i
+  const int Kx = a.K + d, i = lane & 15, g = lane >> 4;
+  float* P = a.part + (size_t)sl * H * Kx;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int b = b0 + 16 * w + 4 * g + q;
-    if (b < a.B) {
-      float* gr = a.G + ((size_t)b * (a.win + 1) + j) * a.d + i;
+  for (int m = 0; m < 4; ++m)
 #pragma unroll
-      for (int ct = 0; ct < DQ; ++ct) gr[16 * ct] = acc[ct][q];
+    for (int n = 0; n < 4; ++n) {
+      const f4 v = lg_sum(hi[m][n], lo[m][n]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        P[(size_t)(64 * wh + 16 * m + 4 * g + r) * Kx + k0 + 64 * wc + 16 * n + i] = v[r];
     }
+}
+
+// =============================================================== G
+//
+// A workgroup takes 64 windows and a range of the entry positions (all of
+// them when the windows alone fill the CUs), ordered context positions, true
+// centre, corrupt.  The windows' vectors of one type sit in LDS as A fragments
+// for every position that uses them; the next type's are in flight in
+// registers meanwhile.  Wave (cg, pg) owns 32 columns and takes every PG-th
+// context position whole (64 x 32 outputs); positions left over, and the two
+// centre entries, are split by windows over the PG groups.  W1's fragments
+// belong to one wave each and come straight from memory, a step ahead.
+template <int CG, int PG>
+__global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
+  constexpr int NT = CG * PG * kWave, D = 32 * CG;
+  constexpr int UPT = (kLgGRows * (kMaxLargeH / 8) + NT - 1) / NT;  // staged units per thread
+  extern __shared__ lu4 lds_q[];  // [H/32 steps][4 row tiles][3][64]
+  const int t = threadIdx.x, lane = t & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int cg = w % CG, pg = w / CG, i = lane & 15, g = lane >> 4;
+  const int b0 = blockIdx.x * kLgGRows, ns = a.H / 32, W1p = a.win + 1;
+  const int o_lo = (int)((int64_t)blockIdx.y * W1p / gridDim.y);
+  const int o_hi = (int)((int64_t)(blockIdx.y + 1) * W1p / gridDim.y);
+  const int nctx = a.win - 1;  // context positions come first
+
+  // unit u: windows 16 (u / 64 % 4) + (u & 15), hidden units 8g.. of step u / 256
+  f4 vr[UPT][2];
+  auto load = [&](int ty) {
+#pragma unroll
+    for (int v = 0; v < UPT; ++v) {
+      const int u = t + v * NT, s = u >> 6;
+      const int b = b0 + 16 * (s & 3) + (u & 15);
+      vr[v][0] = vr[v][1] = kZero4;
+      if (s < 4 * ns && b < a.B) {
+        const float* src = a.V + ((size_t)b * 3 + ty) * a.H + 32 * (s >> 2) + 8 * ((u >> 4) & 3);
+        vr[v][0] = ld4(src);
+        vr[v][1] = ld4(src + 4);
+      }
+    }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int v = 0; v < UPT; ++v) {
+      const int u = t + v * NT, s = u >> 6;
+      if (s < 4 * ns) {
+        float x[8];
+        lu4 p[3];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = vr[v][e >> 2][e & 3];
+        lg_split8(x, p);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) lds_q[(s * 3 + k) * kWave + (u & 63)] = p[k];
+      }
+    }
+  };
+  auto load_w = [&](int jj, int hs, lu4 (&Bv)[2][3]) {
+    const lu4* src = a.wg + ((size_t)(jj * (D / 16) + 2 * cg) * ns + hs) * 3 * kWave + lane;
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) Bv[n][k] = src[((size_t)n * ns * 3 + k) * kWave];
+  };
+  // position o of the order: entry position and W1 block
+  auto entry = [&](int o) { return o < nctx ? o + (o >= a.c) : (o == nctx ? a.c : a.win); };
+  auto block = [&](int o) { return o < nctx ? o + (o >= a.c) : a.c; };
+  lu4 B0[2][3], B1[2][3];
+  // output rows [16 m0, 16 (m0 + MT)) of position o, whose first two steps'
+  // fragments are loaded; loads those of position on (if >= 0) at the end
+  auto compute = [&](auto mt_c, int m0, int o, int on) {
+    constexpr int MT = decltype(mt_c)::value;
+    f4 hi[MT][2], lo[MT][2];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < 2; ++n) hi[m][n] = lo[m][n] = kZero4;
+    const int jj = block(o), jn = on >= 0 ? block(on) : -1;
+    auto step = [&](int hs, lu4 (&Bv)[2][3]) {
+      lg_step<MT>(lds_q + (hs * 4 + m0) * 3 * kWave + lane, Bv, hi, lo);
+      if (hs + 2 < ns) load_w(jj, hs + 2, Bv);
+      else if (jn >= 0) load_w(jn, hs + 2 - ns, Bv);
+    };
+    for (int hs = 0; hs < ns; hs += 2) {  // ns is even
+      step(hs, B0);
+      step(hs + 1, B1);
+    }
+    const int j = entry(o);
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        const f4 v = lg_sum(hi[m][n], lo[m][n]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int b = b0 + 16 * (m0 + m) + 4 * g + c;
+          if (b < a.B) a.G[((size_t)b * W1p + j) * D + 32 * cg + 16 * n + i] = v[c];
+        }
+      }
+  };
+  constexpr int MS = 4 / PG;  // row tiles of a wave in a position split by windows
+  const int c_hi = min(o_hi, nctx);
+  const int whole = o_lo < c_hi ? (c_hi - o_lo) / PG * PG : 0;  // positions taken whole
+  const int o_s = o_lo + whole;                                 // first one split by windows
+  // this wave's positions in order: o_lo + pg, + PG, ... below o_s, then o_s .. o_hi - 1
+  auto next_of = [&](int o) {
+    const int nx = o < o_s ? (o + PG < o_s ? o + PG : o_s) : o + 1;
+    return nx < o_hi ? nx : -1;
+  };
+  auto type_of = [&](int o) { return o < nctx ? 0 : (o == nctx ? 1 : 2); };
+  int o = whole > 0 ? o_lo + pg : o_s;
+  load_w(block(o), 0, B0);
+  load_w(block(o), 1, B1);
+  load(type_of(o_lo));
+  store();
+  __syncthreads();
+  int ty = type_of(o_lo);
+  const int ty_last = type_of(o_hi - 1);
+  if (ty < ty_last) load(ty + 1);
+  while (o >= 0) {
+    if (type_of(o) != ty) {  // every wave reaches a new type at the same position
+      __syncthreads();
+      store();
+      __syncthreads();
+      ++ty;
+      if (ty < ty_last) load(ty + 1);
+    }
+    const int on = next_of(o);
+    if (PG == 1 || o < o_s) compute(std::integral_constant<int, 4>{}, 0, o, on);
+    else compute(std::integral_constant<int, MS>{}, MS * pg, o, on);
+    o = on;
   }
 }
 

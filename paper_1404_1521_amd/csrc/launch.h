@@ -1,5 +1,6 @@
 // Argument blocks and launchers shared by kernels.hip and the host API.
 #pragma once
+#include <algorithm>
 #include <tuple>
 #include <utility>
 
@@ -62,9 +63,43 @@ struct FwdArgs {
 };
 
 // Three-contraction path (hidden layer above 64 units).
-constexpr int kLgRows = 32;        // windows per forward workgroup
-constexpr int kLgSlice = 1024;     // windows per dW1 slice
+typedef uint32_t lu4 __attribute__((ext_vector_type(4)));
+constexpr int kLgMaxSlice = 2048;  // most windows of a dW1 slice (its ids sit in LDS)
 constexpr int kLgGRows = 64;       // windows per G workgroup
+
+// 16-window tiles per forward workgroup: the fewest (1, 2 or 4) that need at
+// most one workgroup per CU, so that small batches spread over the chip;
+// larger ones reread W1 less.
+inline int large_fwd_mt(int B) {
+  return B <= 16 * kCus ? 1 : (B <= 32 * kCus ? 2 : 4);
+}
+inline int large_fwd_grid(int B) { return ceil_div(B, 16 * large_fwd_mt(B)); }
+
+// Columns of a dW1 workgroup: 128 when they stay inside one window position.
+inline int large_dw1_cols(int d) { return d % 128 == 0 ? 128 : 64; }
+
+// LDS of a dW1 workgroup: both operands of two 32-window steps in three
+// bfloat16 terms, and the slice's row ids.
+inline size_t large_dw1_lds(int H, int d, int slice) {
+  return (size_t)2 * 32 * 6 * (H + large_dw1_cols(d)) + (size_t)slice * 4;
+}
+
+// Windows per dW1 slice, a multiple of the 32 of a step: as many slices as
+// fill the CUs once (twice where two workgroups fit a CU's LDS).
+inline int large_dw1_slice(int H, int d, int win, int B) {
+  const int ncol = (win + 1) * d / large_dw1_cols(d);
+  const int fit = large_dw1_lds(H, d, kLgMaxSlice) * 2 <= (size_t)kMaxLdsBytes ? 2 : 1;
+  const int steps = ceil_div(B, 32);
+  const int n = std::max(1, std::min(fit * kCus / ncol, steps));
+  return std::min(ceil_div(steps, n) * 32, kLgMaxSlice);
+}
+// Most slices of any batch up to max_batch (their number falls with B only
+// where the slice length steps up).
+inline int large_dw1_max_slices(int H, int d, int win, int max_batch) {
+  const int ncol = (win + 1) * d / large_dw1_cols(d);
+  return std::max({1, std::min(2 * kCus / ncol, ceil_div(max_batch, 32)),
+                   ceil_div(max_batch, kLgMaxSlice)});
+}
 
 struct LargeArgs {
   const float* E;
@@ -76,11 +111,15 @@ struct LargeArgs {
   const int32_t* corrupt;
   float* V;          // [B][3][H]
   float* vpart;      // [forward workgroups][2H + 2]: db1, dw2, loss, db2
-  float* part;       // [slices][H][K] dW1 partials
+  float* part;       // [slices][H][K + d] dW1 partials; columns K..: the corrupt rows' share
+                     // of the centre block
   float* G;          // [B*(win+1)][d]
   float* scores;     // score-only mode: s(x) [B]
+  lu4* wf;           // W1's fragments for the forward
+  lu4* wg;           // ... and for G
   uint32_t* flag;
   int V_rows, d, win, H, K, c, B;
+  int slice, n_slices;  // windows per dW1 slice, slices
   float invB;
 };
 
@@ -103,6 +142,9 @@ struct DenseArgs {
   // 2: the partial slots come in pairs (2q, 2q+1) that each hold half of the
   // dW1 output tiles (tile L = (k / 16) (Hp / 16) + n / 16 in slot 2q + L % 2)
   int split;
+  // kx > 0: a dW1 slot has kx further columns [Hp][K + kx], whose values add to
+  // columns c0 .. c0 + kx
+  int kx, c0;
   float lr, invB;
 };
 
@@ -241,7 +283,9 @@ hipError_t launch_apply_part(const ApplyArgs& a, int grid, const Launch& L);
 hipError_t launch_check_idx(const int32_t* idx, int N, int rows, uint32_t* flag, const Launch& L);
 hipError_t launch_score(const ScoreArgs& a, int NT, int cpw, const Launch& L);
 hipError_t launch_gather(const GatherArgs& a, const Launch& L);
-// three-contraction path: forward (or score only), dW1 partials, G rows
+// three-contraction path: W1's fragments, forward (or score only), dW1
+// partials, G rows
+hipError_t launch_large_prep(const LargeArgs& a, const Launch& L);
 hipError_t launch_large_fwd(const LargeArgs& a, int score_only, const Launch& L);
 hipError_t launch_large_dw1(const LargeArgs& a, const Launch& L);
 hipError_t launch_large_g(const LargeArgs& a, const Launch& L);

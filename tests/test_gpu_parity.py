@@ -617,6 +617,36 @@ def test_large_hidden_layer_shapes(w, mode):
     run_both(w, w.steps, w.B, mode)
 
 
+# The wide path's other forms: 32 and 64 windows per forward workgroup (from
+# 4,097 and 8,193 windows), every column grouping of the rows G (d 64 .. 256),
+# one and two workgroups per position range, window 1 (no context positions),
+# batches one past a 16-, 32- or 64-window tile.
+@pytest.mark.parametrize("d,win,H,B", [(128, 3, 128, 4097), (64, 3, 192, 8193), (256, 1, 128, 33),
+                                       (128, 1, 256, 65), (192, 3, 256, 17)])
+def test_wide_forms(d, win, H, B):
+    w = workloads.Workload(f"w{win}_d{d}_h{H}", V=2500, d=d, win=win, H=H, B=B, lr=0.05, steps=1,
+                           zipf_s=1.0, seed=24)
+    p = run_both(w, 1, B)[1]
+    ids, _ = workloads.batch(w, 1, B)
+    got = host(pg().Context(w.V, d, win, H, max_batch=B).score(params_dev(p), dev(ids)))
+    np.testing.assert_allclose(got, oracle.score(p, ids), rtol=1e-5, atol=1e-6)
+
+
+def test_wide_scores_of_infinite_rows():
+    """An infinite parameter saturates its windows' hidden units (tanh of an
+    infinity is 1), whatever form the contraction takes: the scores stay
+    finite and equal the oracle's; a NaN reaches its own windows only."""
+    w = workloads.Workload("w3_d64_h128", V=50, d=64, win=3, H=128, B=40, lr=0.05, steps=1,
+                           zipf_s=1.0, seed=25)
+    p = workloads.init_params(w)
+    p["E"][7, 5], p["E"][20, 63], p["E"][33, 0] = np.inf, -np.inf, np.nan
+    ids = np.arange(3 * w.B, dtype=np.int32).reshape(w.B, 3) % w.V
+    got = host(pg().Context(w.V, w.d, w.win, w.H, max_batch=w.B).score(params_dev(p), dev(ids)))
+    nan = (ids == 33).any(1)
+    assert np.isnan(got[nan]).all() and np.isfinite(got[~nan]).all()
+    np.testing.assert_allclose(got[~nan], oracle.score(p, ids)[~nan], rtol=1e-5, atol=1e-6)
+
+
 @pytest.mark.parametrize("w", LARGE_SHAPES[:2], ids=[w.name for w in LARGE_SHAPES[:2]])
 def test_large_hidden_layer_scores(w):
     p = workloads.init_params(w)
