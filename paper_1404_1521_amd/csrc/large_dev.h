@@ -75,32 +75,45 @@ __device__ __forceinline__ f4 lg_sum(f4 hi, f4 lo) {
   return r;
 }
 
-// hi/lo[m][n] += A_m B[n] over one 32-term step, A_m's three fragments at
-// s + 192 m: row tiles in pairs, product-major, so that four accumulators
-// separate dependent instructions and few operand registers are live.
+// A group of a 32-term step: P row tiles x 2 column tiles, hi/lo[m][n] +=
+// A_m B[n], product-major (dependent instructions on one accumulator issue
+// back to back at full rate).
+template <int P>
+__device__ __forceinline__ void lg_read(const lu4* s, lu4 (&A)[P][3]) {
+#pragma unroll
+  for (int v = 0; v < P; ++v)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) A[v][k] = s[(v * 3 + k) * kWave];
+}
+template <int P, int MT>
+__device__ __forceinline__ void lg_group(const lu4 (&A)[P][3], const lu4 (&Bv)[2][3], int m0,
+                                         f4 (&hi)[MT][2], f4 (&lo)[MT][2]) {
+  constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+  for (int p = 0; p < 5; ++p)
+#pragma unroll
+    for (int v = 0; v < P; ++v)
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+        lo[m0 + v][n] = lg_mfma(A[v][PA[p]], Bv[n][PB[p]], lo[m0 + v][n]);
+#pragma unroll
+  for (int v = 0; v < P; ++v)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) hi[m0 + v][n] = lg_mfma(A[v][0], Bv[n][0], hi[m0 + v][n]);
+}
+// Keeps the reads issued above it ahead of the instructions below it.
+__device__ __forceinline__ void lg_pin() { __builtin_amdgcn_sched_barrier(0); }
+
+// One 32-term step of MT row tiles (fragments at s), row tiles in pairs.
 template <int MT>
 __device__ __forceinline__ void lg_step(const lu4* s, const lu4 (&Bv)[2][3], f4 (&hi)[MT][2],
                                         f4 (&lo)[MT][2]) {
-  constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};
   constexpr int P = MT > 1 ? 2 : 1;
 #pragma unroll
   for (int m = 0; m < MT; m += P) {
     lu4 A[P][3];
-#pragma unroll
-    for (int v = 0; v < P; ++v)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) A[v][k] = s[((m + v) * 3 + k) * kWave];
-#pragma unroll
-    for (int p = 0; p < 5; ++p)
-#pragma unroll
-      for (int v = 0; v < P; ++v)
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-          lo[m + v][n] = lg_mfma(A[v][PA[p]], Bv[n][PB[p]], lo[m + v][n]);
-#pragma unroll
-    for (int v = 0; v < P; ++v)
-#pragma unroll
-      for (int n = 0; n < 2; ++n) hi[m + v][n] = lg_mfma(A[v][0], Bv[n][0], hi[m + v][n]);
+    lg_read<P>(s + m * 3 * kWave, A);
+    lg_group<P, MT>(A, Bv, m, hi, lo);
   }
 }
 
@@ -173,6 +186,9 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
   const int w = __builtin_amdgcn_readfirstlane(t / kWave);
   const int i = lane & 15, g = lane >> 4;
   const int r0 = blockIdx.x * R;
+  // one wave of each SIMD goes first, so the two drift apart and one's reads
+  // and epilogues run under the other's matrix instructions
+  if (w >= NW / 2) __builtin_amdgcn_s_setprio(1);
   const int W1p = a.win + 1, d = a.d;
   if (t < R) badrow[t] = 0;
   __syncthreads();
@@ -203,7 +219,7 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
 #pragma unroll
     for (int v = 0; v < UPT; ++v) {
       const int u = t + v * NT;
-      if (u < UN) {
+      if (UN % NT == 0 || u < UN) {
         const int r = 16 * (u >> 7) + (u & 15), col = off + 32 * ((u >> 6) & 1) + 8 * ((u >> 4) & 3);
         const float* src = a.E + (size_t)ids[r][jb] * d + col;
         X[v][0] = ld4(src);
@@ -220,7 +236,7 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
 #pragma unroll
     for (int v = 0; v < UPT; ++v) {
       const int u = t + v * NT;
-      if (u < UN) {
+      if (UN % NT == 0 || u < UN) {
         const int slot = (((u >> 6) & 1) * MT + (u >> 7)) * 3 * kWave + (u & 63);
         float x[8];
         lu4 p[3];
@@ -252,28 +268,55 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
 #pragma unroll
     for (int n = 0; n < 2; ++n) zh[m][n] = zl[m][n] = D[m][n] = kZero4;
   lu4 B0[2][3], B1[2][3];
-  load(0);
-  load_w(0, 0, B0);
-  load_w(0, 1, B1);
   f4 dh[MT][2], dl[MT][2];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int n = 0; n < 2; ++n) dh[m][n] = dl[m][n] = kZero4;
-  // chunk q, in buffer q & 1: one barrier each (the buffer written at chunk q
-  // was last read at chunk q - 2, before chunk q - 1's barrier)
+  // the next chunk's rows into the other buffer, the one after that into registers
+  auto stage = [&](int q) {
+    if (q + 1 < nch) {
+      if (!SCORE && q + 1 < dch) store(std::true_type{}, (q + 1) & 1);
+      else store(std::false_type{}, (q + 1) & 1);
+    }
+    if (q + 2 < nch) load(q + 2);
+  };
+  load(0);
+  load_w(0, 0, B0);
+  load_w(0, 1, B1);
+  store(std::integral_constant<bool, !SCORE>{}, 0);
+  if (nch > 1) load(1);
+  __syncthreads();
+  // chunk q, in buffer q & 1: one barrier each.  The two waves of a SIMD stage
+  // at opposite ends of the chunk, so that one splits while the other multiplies.
   auto chunk = [&](auto centre, int q) {
     const int buf = q & 1;
-    store(centre, buf);
-    if (q + 1 < nch) load(q + 1);
-    __syncthreads();
+    if (w < NW / 2) stage(q);
+    const int qn = min(q + 1, nch - 1);  // (the last chunk's own again: not used)
+    if constexpr (decltype(centre)::value) {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      lu4 (&Bv)[2][3] = ks ? B1 : B0;
-      lg_step<MT>(&Xs[buf][ks * SF + lane], Bv, zh, zl);
-      if constexpr (decltype(centre)::value) lg_step<MT>(&Ts[buf][ks * SF + lane], Bv, dh, dl);
-      if (q + 1 < nch) load_w(q + 1, ks, Bv);
+      for (int ks = 0; ks < 2; ++ks) {
+        lu4 (&Bv)[2][3] = ks ? B1 : B0;
+        lg_step<MT>(&Xs[buf][ks * SF + lane], Bv, zh, zl);
+        lg_step<MT>(&Ts[buf][ks * SF + lane], Bv, dh, dl);
+        load_w(qn, ks, Bv);
+      }
+    } else {
+      constexpr int P = MT > 1 ? 2 : 1, GS = MT / P;  // groups of a step
+      const lu4* s = &Xs[buf][lane];
+      lu4 A[2][P][3];
+      lg_read<P>(s, A[0]);
+#pragma unroll
+      for (int gr = 0; gr < 2 * GS; ++gr) {
+        if (gr + 1 < 2 * GS) lg_read<P>(s + (gr + 1) * P * 3 * kWave, A[(gr + 1) & 1]);
+        lg_pin();
+        lg_group<P, MT>(A[gr & 1], gr / GS ? B1 : B0, gr % GS * P, zh, zl);
+        lg_pin();
+        if (gr % GS == GS - 1) load_w(qn, gr / GS, gr / GS ? B1 : B0);
+      }
     }
+    if (w >= NW / 2) stage(q);
+    __syncthreads();
   };
   int q = 0;
   if constexpr (!SCORE) {
@@ -422,6 +465,7 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
   const int t = threadIdx.x, lane = t & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(t / kWave);
   const int wh = w % HW, wc = w / HW;
+  if (2 * w >= HW * CW) __builtin_amdgcn_s_setprio(1);  // (as in k_large_fwd)
   const int d = a.d, ncol = (a.K + d) / CB, nwg = ncol * a.n_slices;
   const int per = (nwg + kXcds - 1) / kXcds;
   const int f = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
@@ -440,20 +484,33 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
 
   const float* vbase = a.V + (size_t)b_lo * 3 * H + (size_t)ty * H;
   float vr[VU][8], xr[XU][8];
-  auto load = [&](int st) {
+  auto load_t = [&](auto tail, int st) {  // tail: the step has windows past the slice
+    constexpr bool TAIL = decltype(tail)::value;
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
-      const int x = t + u * NT, h = x % H, r = 32 * st + 8 * (x / H);
+      const int x = t + u * NT, r = 32 * st + 8 * (x / H);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) vr[u][e] = r + e < nb ? vbase[(size_t)(r + e) * 3 * H + h] : 0.f;
+      for (int e = 0; e < 8; ++e) {
+        const int re = TAIL ? min(r + e, nb - 1) : r + e;
+        vr[u][e] = vbase[re * 3 * H + x % H];
+        if (TAIL && r + e >= nb) vr[u][e] = 0.f;
+      }
     }
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
-      const int x = t + u * NT, col = x % CB, r = 32 * st + 8 * (x / CB);
+      const int x = t + u * NT, r = 32 * st + 8 * (x / CB);
+      if (CB * 4 % NT == 0 || x < CB * 4) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        xr[u][e] = x < CB * 4 && r + e < nb ? a.E[(size_t)ids[r + e] * d + off0 + col] : 0.f;
+        for (int e = 0; e < 8; ++e) {
+          const int re = TAIL ? min(r + e, nb - 1) : r + e;
+          xr[u][e] = a.E[(size_t)ids[re] * d + off0 + x % CB];
+        }
+      }
     }
+  };
+  auto load = [&](int st) {
+    if (32 * st + 32 <= nb) load_t(std::false_type{}, st);
+    else load_t(std::true_type{}, st);
   };
   auto store = [&](int buf) {
     lu4 p[3];
@@ -468,7 +525,7 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
       const int x = t + u * NT, col = x % CB, gq = x / CB;
-      if (x < CB * 4) {
+      if (CB * 4 % NT == 0 || x < CB * 4) {
         lg_split8(xr[u], p);
 #pragma unroll
         for (int k = 0; k < 3; ++k)
@@ -486,31 +543,39 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
   if (steps > 1) load(1);
   __syncthreads();
   // step st reads buffer st & 1 and fills the other one, last read at step
-  // st - 1, before its closing barrier
+  // st - 1, before its closing barrier.  The two waves of a SIMD stage at
+  // opposite ends of the step, so that one splits while the other multiplies.
+  auto stage = [&](int st) {
+    if (st + 1 < steps) store((st + 1) & 1);
+    if (st + 2 < steps) load(st + 2);
+  };
   for (int st = 0; st < steps; ++st) {
     const int buf = st & 1;
-    if (st + 1 < steps) store(buf ^ 1);
-    if (st + 2 < steps) load(st + 2);
+    if (2 * w < HW * CW) stage(st);
     const lu4* vs = Vs + buf * VF + wh * 4 * 3 * kWave + lane;
     const lu4* xs = Xs + buf * XF + wc * 4 * 3 * kWave + lane;
-    lu4 A[4][3];
+    lu4 A[4][3], Bv[2][3];
+    lg_read<4>(vs, A);
+    auto read_b = [&](int n, lu4 (&Bn)[3]) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) A[m][k] = vs[(m * 3 + k) * kWave];
+      for (int k = 0; k < 3; ++k) Bn[k] = xs[(n * 3 + k) * kWave];
+    };
+    read_b(0, Bv[0]);
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      lu4 Bv[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) Bv[k] = xs[(n * 3 + k) * kWave];
+      if (n < 3) read_b(n + 1, Bv[(n + 1) & 1]);
+      lg_pin();
+      const lu4 (&Bn)[3] = Bv[n & 1];
       constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};
 #pragma unroll
       for (int p = 0; p < 5; ++p)
 #pragma unroll
-        for (int m = 0; m < 4; ++m) lo[m][n] = lg_mfma(A[m][PA[p]], Bv[PB[p]], lo[m][n]);
+        for (int m = 0; m < 4; ++m) lo[m][n] = lg_mfma(A[m][PA[p]], Bn[PB[p]], lo[m][n]);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) hi[m][n] = lg_mfma(A[m][0], Bv[0], hi[m][n]);
+      for (int m = 0; m < 4; ++m) hi[m][n] = lg_mfma(A[m][0], Bn[0], hi[m][n]);
+      lg_pin();
     }
+    if (2 * w >= HW * CW) stage(st);
     __syncthreads();
   }
   // lane (i, g), component r: hidden 64 wh + 16m + 4g + r, column k0 + 64 wc + 16n + i
@@ -532,8 +597,7 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
 // A workgroup takes 64 windows and a range of the entry positions (all of
 // them when the windows alone fill the CUs), ordered context positions, true
 // centre, corrupt.  The windows' vectors of one type sit in LDS as A fragments
-// for every position that uses them; the next type's are in flight in
-// registers meanwhile.  Wave (cg, pg) owns 32 columns and takes every PG-th
+// for every position that uses them.  Wave (cg, pg) owns 32 columns and takes every PG-th
 // context position whole (64 x 32 outputs); positions left over, and the two
 // centre entries, are split by windows over the PG groups.  W1's fragments
 // belong to one wave each and come straight from memory, a step ahead.
@@ -545,6 +609,7 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
   const int t = threadIdx.x, lane = t & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(t / kWave);
   const int cg = w % CG, pg = w / CG, i = lane & 15, g = lane >> 4;
+  if (2 * w >= CG * PG) __builtin_amdgcn_s_setprio(1);  // (as in k_large_fwd)
   const int b0 = blockIdx.x * kLgGRows, ns = a.H / 32, W1p = a.win + 1;
   const int o_lo = (int)((int64_t)blockIdx.y * W1p / gridDim.y);
   const int o_hi = (int)((int64_t)(blockIdx.y + 1) * W1p / gridDim.y);
@@ -641,14 +706,13 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
   __syncthreads();
   int ty = type_of(o_lo);
   const int ty_last = type_of(o_hi - 1);
-  if (ty < ty_last) load(ty + 1);
   while (o >= 0) {
     if (type_of(o) != ty) {  // every wave reaches a new type at the same position
       __syncthreads();
+      load(ty + 1);
       store();
       __syncthreads();
       ++ty;
-      if (ty < ty_last) load(ty + 1);
     }
     const int on = next_of(o);
     if (PG == 1 || o < o_s) compute(std::integral_constant<int, 4>{}, 0, o, on);
