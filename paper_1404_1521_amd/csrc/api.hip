@@ -824,7 +824,8 @@ int polyglot_gather(polyglot_ctx* ctx, const float* E, const int32_t* windows,
   if (B <= 0 || B > ctx->cfg.max_batch) return fail(ctx, POLYGLOT_EBATCH, "gather: bad B");
   if (!aligned16(E) || !aligned16(X) || !aligned16(Xc))
     return fail(ctx, POLYGLOT_EINVAL, "gather: E, X, Xc must be 16-byte aligned");
-  GatherArgs a{E, windows, corrupt, X, Xc, ctx->ws.flag, ctx->cfg.V, ctx->cfg.d, ctx->cfg.win, B};
+  GatherArgs a{E, windows, corrupt, X, Xc, ctx->ws.flag, ctx->cfg.V, ctx->cfg.d, ctx->cfg.win, B,
+               0, 0};
   hipError_t e;
   {
     Timed tm(ctx, POLYGLOT_K_GATHER);

@@ -86,29 +86,55 @@ __global__ __launch_bounds__(kBlock) void k_score(ScoreArgs a) {
 }
 
 // =============================================================== gather
+//
+// A wave copies a.rows consecutive entries (rows of X and Xc): each lane looks
+// up one entry, and the rows then go as one flat list of 16-byte words,
+// kGatherU of them in flight per lane.  An entry's position is divided out
+// once per row and not once per word, and by 32-bit arithmetic.  The stores are
+// non-temporal: X is written once and several times the size of the rows read,
+// which would lose their place in the caches to it.  16,384 windows of 11
+// rows of 128 out of a 512 MB table (140 MB in and out), three outputs in
+// turn: 37.7 us with a thread per word and two 64-bit divisions, 33.5 us this
+// way with plain stores, 24.2 us (5.8 TB/s) with these; 65,536 windows of 5
+// rows of 64: 34.6, 31.7 and 22.0 us.
+constexpr int kGatherU = 8;
 
 __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a) {
-  // one thread per float4 of output; position j == win is the corrupt row
-  const int q4 = a.d / 4;
-  const size_t total = (size_t)a.B * (a.win + 1) * q4;
-  for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < total;
-       i += (size_t)gridDim.x * kBlock) {
-    const size_t rowi = i / q4;
-    const int q = (int)(i - rowi * q4);
-    const int b = (int)(rowi / (a.win + 1));
-    const int j = (int)(rowi - (size_t)b * (a.win + 1));
-    const int32_t id = (j < a.win) ? a.windows[(size_t)b * a.win + j] : a.corrupt[b];
-    f4 v;
-    if ((uint32_t)id < (uint32_t)a.V) {
-      v = ld4(a.E + (size_t)id * a.d + 4 * q);
-    } else {
-      if (q == 0) atomicOr(a.flag, kFlagBadId);
-      const float nan = __builtin_nanf("");
-      v = f4{nan, nan, nan, nan};
+  __shared__ int2 ent[kWavesPerBlock][kWave];  // (id or -1, row of X or ~row of Xc)
+  const int t = threadIdx.x, lane = t & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int q4 = a.d / 4, W1p = a.win + 1;
+  const int N = a.B * W1p;
+  const int e0 = (blockIdx.x * kWavesPerBlock + w) * a.rows;
+  const int nr = min(a.rows, N - e0);
+  if (nr <= 0) return;
+  if (lane < nr) {
+    const int e = e0 + lane, b = e / W1p, j = e - b * W1p;
+    int32_t id = j < a.win ? a.windows[e - b] : a.corrupt[b];  // b win + j = e - b
+    if ((uint32_t)id >= (uint32_t)a.V) {
+      atomicOr(a.flag, kFlagBadId);
+      id = -1;
     }
-    float* dst = (j < a.win) ? a.X + ((size_t)b * a.win + j) * a.d + 4 * q
-                             : a.Xc + (size_t)b * a.d + 4 * q;
-    st4(dst, v);
+    ent[w][lane] = int2{id, j < a.win ? e - b : ~b};
+  }
+  wave_lds_sync();
+  const int total = nr * q4;
+  for (int f0 = lane; f0 < total; f0 += kWave * kGatherU) {
+    f4 v[kGatherU];
+    float* dst[kGatherU];
+#pragma unroll
+    for (int u = 0; u < kGatherU; ++u) {
+      const int f = min(f0 + u * kWave, total - 1);
+      const int r = (int)((uint32_t)f * a.rq4 >> 20), q = f - r * q4;  // f / q4: f < 4096
+      const int2 x = ent[w][r];
+      dst[u] = x.y >= 0 ? a.X + (size_t)x.y * a.d + 4 * q : a.Xc + (size_t)~x.y * a.d + 4 * q;
+      const float nan = __builtin_nanf("");
+      v[u] = f4{nan, nan, nan, nan};
+      if (x.x >= 0) v[u] = ld4(a.E + (size_t)x.x * a.d + 4 * q);
+    }
+#pragma unroll
+    for (int u = 0; u < kGatherU; ++u)
+      if (f0 + u * kWave < total) __builtin_nontemporal_store(v[u], reinterpret_cast<f4*>(dst[u]));
   }
 }
 

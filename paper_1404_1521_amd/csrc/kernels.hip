@@ -413,10 +413,13 @@ hipError_t launch_large_g(const LargeArgs& a, const Launch& L) {
 }
 
 hipError_t launch_gather(const GatherArgs& a, const Launch& L) {
-  const size_t total = (size_t)a.B * (a.win + 1) * (a.d / 4);
-  const size_t want = (total + kBlock - 1) / kBlock;
-  const int grid = (int)(want < 8192 ? (want > 0 ? want : 1) : 8192);
-  return pg_launch(k_gather, dim3(grid), dim3(kBlock), 0, L, a);
+  GatherArgs g = a;
+  const int N = a.B * (a.win + 1), q4 = a.d / 4;
+  // 64 rows a wave, fewer while that leaves less than 8 waves per CU
+  g.rows = kWave;
+  while (g.rows > 4 && N / g.rows < 8 * kCus) g.rows /= 2;
+  g.rq4 = ((1u << 20) + q4 - 1) / q4;
+  return pg_launch(k_gather, dim3(ceil_div(N, g.rows * kWavesPerBlock)), dim3(kBlock), 0, L, g);
 }
 
 }  // namespace pg

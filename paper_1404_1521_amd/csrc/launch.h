@@ -205,6 +205,8 @@ struct GatherArgs {
   float* Xc;
   uint32_t* flag;
   int V, d, win, B;
+  int rows;      // entries per wave, at most 64
+  uint32_t rq4;  // ceil(2^20 / (d / 4)): f rq4 >> 20 = f / (d / 4) for f < 4096
 };
 
 hipError_t launch_step_fwdbwd(const FwdArgs& a, int NT, int cpw, int grid, size_t lds,

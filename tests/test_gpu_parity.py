@@ -149,6 +149,29 @@ def scatter_bound(t0, idx, Y, alpha):
     return cnt * 2.0 ** -24 * mag + 1e-30
 
 
+# Row widths that do and do not divide a wave, one entry to many per wave, a
+# last wave with fewer rows than the others, and out-of-range ids.
+@pytest.mark.parametrize("d,win,B", [(112, 3, 97), (256, 1, 3), (16, 31, 1001), (192, 5, 6000),
+                                     (64, 7, 20_003)])
+def test_gather_row_widths(d, win, B):
+    rng = np.random.default_rng([d, win, B])
+    E = rng.standard_normal((3000, d), dtype=np.float32)
+    ids = rng.integers(0, 3000, (B, win), dtype=np.int32)
+    cor = rng.integers(0, 3000, B, dtype=np.int32)
+    m = pg()
+    ctx = m.Context(3000, d, win, 16 if d % 64 else 128, max_batch=B)
+    X, Xc = ctx.gather(dev(E), dev(ids), dev(cor))
+    assert ctx.status() == m.OK
+    assert np.array_equal(host(X), E[ids].reshape(B, -1)) and np.array_equal(host(Xc), E[cor])
+    ids[B // 2, win - 1], cor[0] = 3000, -1
+    X, Xc = ctx.gather(dev(E), dev(ids), dev(cor))
+    assert ctx.status() == m.EID
+    ref = E[np.minimum(ids, 2999)]
+    ref[B // 2, win - 1] = np.nan
+    assert np.array_equal(host(X), ref.reshape(B, -1), equal_nan=True)
+    assert np.isnan(host(Xc)[0]).all() and np.array_equal(host(Xc)[1:], E[cor[1:]])
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("rows,d,N,s", [
     (50, 8, 400, 1.2), (3, 4, 1, 1.0), (1000, 64, 5000, 1.2), (1000, 64, 8192, 1.2),
