@@ -55,6 +55,7 @@ struct polyglot_ctx {
   std::string err;
   bool have_sorted = false;
   int last_N = 0, last_passes = 0, last_set = 0;
+  bool set_dirty = false;  // an assignment marked its rows and failed to take the marks back
   hipGraphExec_t gexec = nullptr;
   GraphKey gkey{};
   bool gvalid = false;
@@ -651,7 +652,10 @@ int polyglot_init(const polyglot_config* cfg, void* stream, polyglot_ctx** out) 
     // pair its own
     e = alloc(ctx, &ws.part, (size_t)2 * ctx->max_parts * ctx->part_stride);
   }
-  if (e == hipSuccess) e = alloc(ctx, &ws.seg_end, (size_t)std::max(c.V, c.max_rows));
+  // one block with the assignment's marks, which start at zero
+  const size_t n_end = (size_t)std::max(c.V, c.max_rows);
+  if (e == hipSuccess) e = alloc(ctx, &ws.seg_end, n_end + c.max_rows);
+  ws.last = ws.seg_end + n_end;
   if (e == hipSuccess) e = alloc(ctx, &ws.seg_part, (size_t)ctx->max_chunks * 2 * ctx->seg_stride);
   if (e == hipSuccess) e = alloc(ctx, &ws.long_list, (size_t)ctx->max_chunks);
   if (e == hipSuccess) e = alloc(ctx, &ws.idx32, (size_t)c.max_scatter);
@@ -665,6 +669,7 @@ int polyglot_init(const polyglot_config* cfg, void* stream, polyglot_ctx** out) 
     if (e == hipSuccess) e = hipMemset(ws.tile_ctr[k], 0, sizeof(uint32_t) * kMaxPasses);
   }
   if (e == hipSuccess) e = hipMemset(ws.flag, 0, 3 * sizeof(uint32_t));
+  if (e == hipSuccess && c.max_rows > 0) e = hipMemset(ws.last, 0, sizeof(int32_t) * c.max_rows);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
   for (hipEvent_t* ev : {&ctx->ev_fork, &ctx->ev_sorted[0], &ctx->ev_sorted[1], &ctx->ev_done[0],
                          &ctx->ev_done[1]})
@@ -892,6 +897,26 @@ int polyglot_scatter_update(polyglot_ctx* ctx, void* table, int32_t dtype, int32
     return scatter_add_f32(ctx, static_cast<float*>(table), rows, d, keys,
                            static_cast<const float*>(Y), N, alpha, mode);
   }
+  // bytes per word of an assignment's row copies
+  int set_word = (int)es;
+  for (int wb = 16; wb > (int)es; wb /= 2)
+    if (((size_t)d * es) % wb == 0 && reinterpret_cast<uintptr_t>(table) % wb == 0 &&
+        reinterpret_cast<uintptr_t>(Y) % wb == 0) {
+      set_word = wb;
+      break;
+    }
+  if (op == POLYGLOT_OP_SET && N <= kSetMarkN) {
+    const SetCall c{idx, Y, table, ctx->ws.last, ctx->ws.flag, idx_bytes, rows, N, (int)(d * es),
+                    set_word};
+    Timed tm(ctx, POLYGLOT_K_SCATTER);
+    if (ctx->set_dirty) e = launch_set_clear(ctx->ws.last, ctx->cfg.max_rows, tm.L);
+    if (e == hipSuccess) ctx->set_dirty = false;
+    bool marked = false;
+    if (e == hipSuccess) e = launch_set(c, tm.L, &marked);
+    if (e != hipSuccess && marked) ctx->set_dirty = true;
+    ctx->have_sorted = false;  // as after every call of the op
+    return e == hipSuccess ? POLYGLOT_OK : hip_fail(ctx, e, "scatter_update launch");
+  }
   // the other calls sort the ids as they are (int64 ids narrowed and
   // range-checked by the sort's own key loads)
   const SortPlan plan = make_plan(rows, N);
@@ -923,6 +948,7 @@ int polyglot_scatter_update(polyglot_ctx* ctx, void* table, int32_t dtype, int32
   c.op = op;
   c.n_e = std::max(1, std::min(ceil_div(ceil_div(N, op == POLYGLOT_OP_SET ? kWave : c.ch),
                                         kWavesPerBlock), 2048));
+  c.set_word = set_word;
   c.n_z = plan.small ? 0 : 16;
   // a partitioned (small) list is applied partition-wise, in one launch
   c.part_off = ctx->ws.part_off[0];
@@ -930,13 +956,6 @@ int polyglot_scatter_update(polyglot_ctx* ctx, void* table, int32_t dtype, int32
   c.n_part = 1 << plan.part_bits;  // the partitions this sort wrote
   c.packed = dtype != POLYGLOT_F32 && d % 2 == 0 && reinterpret_cast<uintptr_t>(table) % 4 == 0 &&
              reinterpret_cast<uintptr_t>(Y) % 4 == 0;
-  c.set_word = (int)es;
-  for (int wb = 16; wb > (int)es; wb /= 2)
-    if (((size_t)d * es) % wb == 0 && reinterpret_cast<uintptr_t>(table) % wb == 0 &&
-        reinterpret_cast<uintptr_t>(Y) % wb == 0) {
-      c.set_word = wb;
-      break;
-    }
   if (e == hipSuccess) {
     Timed tm(ctx, POLYGLOT_K_SCATTER);
     e = launch_gen_update(c, tm.L);

@@ -78,6 +78,7 @@ struct Workspace {
   int2* long_list;          // [ranges] by range: (range, row) if a segment crossing
                             // ranges starts there, else (-1, 0)
   int32_t* seg_end;         // [max(V, max_rows)] end range of a long segment, by row id
+  int32_t* last;            // [max_rows] assignment: a row's last entry + 1; zero between calls
   uint32_t* flag;           // sticky error bits [3]: word 0 raised by every launch except a
                             // training step's side-stream sort, word 1 + q by the side-stream
                             // sort of sort set q (read only by that set's update)

@@ -333,7 +333,7 @@ __device__ __forceinline__ void seg_add4(const GenArgs<T>& a, size_t i, int n, f
   seg_put4(a, i, n, seg_row4(a, i, n) + v);
 }
 
-// Assignment: one wave per 64 sorted entries; an entry whose successor has
+// Assignment over a sorted list (long ones): one wave per 64 sorted entries; an entry whose successor has
 // another key (or that is the last) ends its row's segment, so it is the
 // row's last entry in index order, and its Y row is copied.  The error words
 // are read beside the keys.  Each such entry's (entry, row) goes to the
@@ -396,6 +396,98 @@ __global__ __launch_bounds__(kBlock) void k_gen_set(GenArgs<T> a, int n_e) {
     }
     __builtin_amdgcn_wave_barrier();  // the slots are rewritten by the next group
   }
+}
+
+// Assignment of a short list (kSetMarkN): for a repeated index the entry with
+// the largest number wins, so nothing has to be sorted.  k_set_mark leaves in
+// last[row] the largest entry number + 1 of each row; k_set_copy copies the
+// entries that find their own number there and puts the word back to 0 (every
+// other entry of the row reads neither its own number nor has one to put
+// back), so `last` is all zero between calls, whatever they did.
+//
+// What bounds the marking is its atomics: about 10 ns each on the word of one
+// frequent row, about 4 per ns over many rows (327,680 entries: 50 us, where
+// the sort takes 21).  So a workgroup first drops all but the last entry of a
+// repeated row: rows compete for slot row % kSetSlots of a table (the last
+// writer holds it), the holder's entries compete in LDS and one of them goes
+// to memory; entries whose row lost its slot go to memory themselves.
+constexpr int kSetSlots = 2048;
+template <class KeyFn>
+__global__ __launch_bounds__(kBlock) void k_set_mark(KeyFn kf, int N, int32_t* last,
+                                                     uint32_t* flag) {
+  __shared__ int32_t tag[kSetSlots];
+  __shared__ int32_t best[kSetSlots];
+  const int e = blockIdx.x * kBlock + threadIdx.x;
+  const int32_t id = e < N ? kf.load(e) : 0;
+  const bool bad = e < N && (uint32_t)id >= (uint32_t)kf.range;
+  const bool live = e < N && !bad;
+  const int h = (uint32_t)id % kSetSlots;
+  if (live) {
+    tag[h] = id;
+    best[h] = 0;
+  }
+  __syncthreads();
+  const bool mine = live && tag[h] == id;
+  if (mine) atomicMax(&best[h], e + 1);
+  __syncthreads();
+  if (live && (!mine || best[h] == e + 1)) atomicMax(last + id, e + 1);
+  if (__ballot(bad) && lane_id() == 0) atomicOr(flag, kFlagBadId);
+}
+
+// A wave takes a.rows consecutive entries; its winners go to LDS slots by rank
+// and their rows are copied as one flat list of words of W bytes (the widest
+// that divides a row and the pointers' alignment), 8 or 16 words per lane in
+// flight, so a group of short rows takes one round of loads however many it
+// copies.
+struct SetArgs {
+  const void* Y;
+  void* table;
+  int32_t* last;
+  const uint32_t* flag;
+  int N, rows;
+  int dw;         // words per row
+  uint32_t rdw;   // ceil(2^32 / dw), 0 for dw = 1
+};
+template <class W, class KeyFn>
+__global__ __launch_bounds__(kBlock) void k_set_copy(KeyFn kf, SetArgs a) {
+  constexpr int U = sizeof(W) >= 16 ? 8 : 16;
+  __shared__ int2 tl[kWavesPerBlock][kWave];  // (entry, row) of the winners, by rank
+  const int lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int e = (blockIdx.x * kWavesPerBlock + w) * a.rows + lane;
+  const bool act = lane < a.rows && e < a.N;
+  const uint32_t flag = *a.flag;
+  const int32_t id = act ? kf.load(e) : -1;
+  const bool win = (uint32_t)id < (uint32_t)kf.range && a.last[id] == e + 1;
+  if (win) a.last[id] = 0;
+  if (__builtin_amdgcn_readfirstlane(flag) != 0u) return;  // a bad id voids the call
+  const uint64_t wins = __ballot(win);
+  const int rank = __popcll((unsigned long long)(wins & lanemask_lt()));
+  if (win) tl[w][rank] = make_int2(e, id);
+  wave_lds_sync();
+  const W* Yw = static_cast<const W*>(a.Y);
+  W* Tw = static_cast<W*>(a.table);
+  const int total = __popcll((unsigned long long)wins) * a.dw;
+  for (int f0 = lane; f0 < total; f0 += U * kWave) {
+    W v[U];
+    size_t dst[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int f = min(f0 + u * kWave, total - 1);
+      const int j = a.rdw ? (int)__umulhi((uint32_t)f, a.rdw) : f, x = f - j * a.dw;
+      const int2 r = tl[w][j];
+      v[u] = Yw[(size_t)r.x * a.dw + x];
+      dst[u] = (size_t)r.y * a.dw + x;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (f0 + u * kWave < total) Tw[dst[u]] = v[u];
+  }
+}
+
+// Puts `last` back to zero (after a call whose second launch failed).
+__global__ __launch_bounds__(kBlock) void k_set_clear(int32_t* last, int n) {
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) last[i] = 0;
 }
 
 // int64 indices narrowed to int32 keys; an index outside [0, rows) raises

@@ -318,6 +318,34 @@ hipError_t launch_gen_update(const GenCall& c, const Launch& L) {
   return launch_gen_update_t<float>(c, L);
 }
 
+template <class KeyFn>
+static hipError_t launch_set_t(const SetCall& c, const KeyFn& kf, const Launch& L, bool* marked) {
+  const dim3 block(kBlock);
+  const hipError_t e = pg_launch(k_set_mark<KeyFn>, dim3(ceil_div(c.N, kBlock)), block, 0, L, kf,
+                                 c.N, c.last, c.flag);
+  if (e != hipSuccess) return e;
+  *marked = true;
+  SetArgs a{c.Y, c.table, c.last, c.flag, c.N, kWave, c.row_bytes / c.word, 0u};
+  while (a.rows > 8 && c.N / a.rows < 8 * kCus) a.rows /= 2;  // waves for every CU
+  if (a.dw > 1) a.rdw = (uint32_t)(((1ull << 32) + a.dw - 1) / a.dw);
+  const dim3 g2(ceil_div(c.N, a.rows * kWavesPerBlock));
+  if (c.word == 16) return pg_launch(k_set_copy<u32x4, KeyFn>, g2, block, 0, L, kf, a);
+  if (c.word == 8) return pg_launch(k_set_copy<uint64_t, KeyFn>, g2, block, 0, L, kf, a);
+  if (c.word == 4) return pg_launch(k_set_copy<uint32_t, KeyFn>, g2, block, 0, L, kf, a);
+  return pg_launch(k_set_copy<uint16_t, KeyFn>, g2, block, 0, L, kf, a);
+}
+
+hipError_t launch_set(const SetCall& c, const Launch& L, bool* marked) {
+  return c.idx_bytes == 8
+             ? launch_set_t(c, I64Keys{static_cast<const int64_t*>(c.idx), c.range}, L, marked)
+             : launch_set_t(c, IdxKeys{static_cast<const int32_t*>(c.idx), c.range}, L, marked);
+}
+
+hipError_t launch_set_clear(int32_t* last, int n, const Launch& L) {
+  return pg_launch(k_set_clear, dim3(std::min(ceil_div(n, kBlock), 1024)), dim3(kBlock), 0, L,
+                   last, n);
+}
+
 template <class T>
 static hipError_t launch_gen_fix_t(const GenCall& c, int grid, const Launch& L) {
   if (c.partitioned) return hipSuccess;  // the partitions completed every segment

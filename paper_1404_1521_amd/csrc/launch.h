@@ -276,6 +276,30 @@ struct GenCall {
   // widest that divides a row and both pointers' alignment
   int set_word;
 };
+
+// The general op's assignment of a short list: two launches over the entries
+// as they come.
+// marked: whether the first one was made (and `last` needs the second).
+struct SetCall {
+  const void* idx;
+  const void* Y;
+  void* table;
+  int32_t* last;  // [table rows], zero between calls
+  uint32_t* flag;
+  int idx_bytes, range, N;
+  int row_bytes;
+  int word;  // bytes per word of the row copies (as GenCall::set_word)
+};
+// Up to here two launches without a sort, whose atomics cost about 0.25 ns an
+// entry; above, the sort (whose time hardly grows: 16-18 us) and the copies.
+// Same box, us per call, marks against sort (binary16, d 64, Zipf(1.2) into
+// 100,000 rows | float32, d 200, uniform into 300,000 | binary16, d 101,
+// Zipf(1.0) into 600): N = 2000 9.4 against 9.8 | 9.3, 19.6 | 9.3, 20.2;
+// 16,000 9.3, 15.6 | 9.1, 29.8 | 9.4, 19.6; 48,000 14.9, 16.5 | 20.7, 37.1 |
+// 17.9, 17.6; 64,000 18.6, 17.0 | 26.0, 44.8 | 22.1, 17.8.
+constexpr int kSetMarkN = 45056;
+hipError_t launch_set(const SetCall& c, const Launch& L, bool* marked);
+hipError_t launch_set_clear(int32_t* last, int n, const Launch& L);
 hipError_t launch_gen_update(const GenCall& c, const Launch& L);
 hipError_t launch_gen_fix(const GenCall& c, int grid, const Launch& L);
 hipError_t launch_keys_from_i64(const int64_t* idx, int N, int rows, int32_t* keys,

@@ -1259,6 +1259,38 @@ def test_scatter_update_assignment_word_widths(fmt, rows, d, N):
         assert np.array_equal(_to_host(td.contiguous(), fmt), ref), k
 
 
+# The assignment's marks: calls of one context one after another (a mark left
+# behind would decide the next call), a voided call between them, the longest
+# list that is marked and the shortest that is sorted, rows that share a slot
+# of the marking table (ids 2,048 apart), one row only.
+@pytest.mark.parametrize("N,rows,d", [(1, 5, 3), (257, 1, 4), (20_011, 50_000, 100),
+                                      (45_056, 8192, 2), (45_057, 3000, 1)])
+def test_scatter_update_assignment_marks(N, rows, d):
+    m = pg()
+    rng = np.random.default_rng([N, rows])
+    ctx = m.Context(1000, 16, 5, 8, max_batch=1, max_scatter=N, max_rows=rows)
+    table = rng.standard_normal((rows, d)).astype(np.float16)
+    td = dev(table)
+    for rep in range(3):
+        idx = workloads.zipf_ids(rng, rows, 1.0, N).astype(np.int64)
+        if rep == 1 and rows > 2048:
+            idx = idx // 2048 * 2048 + rng.integers(0, 2, N)
+            idx = np.minimum(idx, rows - 1)
+        Y = rng.standard_normal((N, d)).astype(np.float16)
+        if rep == 2:  # voided: nothing written, no mark left
+            bad = idx.copy()
+            bad[N // 2] = rows
+            ctx.scatter_update(td, dev(bad), dev(Y), op=m.OP_SET)
+            assert ctx.status() == m.EID
+            assert np.array_equal(host(td), table)
+        ctx.scatter_update(td, dev(idx if rep else idx.astype(np.int32)), dev(Y), op=m.OP_SET)
+        assert ctx.status() == m.OK
+        last = np.full(rows, -1)
+        np.maximum.at(last, idx, np.arange(N))
+        table[last >= 0] = Y[last[last >= 0]]
+        assert np.array_equal(host(td), table)
+
+
 @pytest.mark.parametrize("fmt", ["bf16", "f16"])
 def test_scatter_update_int64_ids_lookback_sort(fmt):
     """int64 ids are narrowed and range-checked by the sort's own key loads
