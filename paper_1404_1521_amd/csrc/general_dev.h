@@ -97,7 +97,7 @@ struct GenArgsP : GenArgs<T> {
   static constexpr bool kPacked = true;
 };
 
-template <class T>
+template <bool STREAM, class T>
 __device__ __forceinline__ float seg_load(const GenArgs<T>& a, size_t i) {
   return Elem<T>::get(a.Y[i]);
 }
@@ -190,7 +190,7 @@ __device__ __forceinline__ uint32_t pack2(float x, float y) {
   return (uint32_t)Elem<T>::put(x).bits | ((uint32_t)Elem<T>::put(y).bits << 16);
 }
 
-template <int CH, class A>
+template <int CH, bool STREAM, class A>
 __device__ void seg_walk_packed(const A& a, const ChunkInfo& ci, uint64_t tails, uint64_t complete,
                                 int first_tail, bool starts_long, const ChunkSink& sink) {
   using T = typename A::elem;
