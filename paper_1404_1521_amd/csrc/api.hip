@@ -376,6 +376,7 @@ int enqueue_compute(polyglot_ctx* ctx, float* E, float* W1, float* b1, float* w2
     fa.sb = sort_bufs(ctx, set);
     fa.ntiles = ceil_div(B, kTileRows);
     const int shape8 = fwdbwd8_shape(cf.d, cf.win, ctx->NT);
+    const bool split3 = shape8 == 1 && fa.n_sort == 0 && B >= kFsMinBatch;
     fa.tiles_per_wg = ceil_div(fa.ntiles, shape8 ? std::min(ctx->max_parts, kF8MaxWorkgroups)
                                                  : ctx->max_parts);
     // the pair form takes an even number of tiles per workgroup
@@ -388,12 +389,20 @@ int enqueue_compute(polyglot_ctx* ctx, float* E, float* W1, float* b1, float* w2
     fa.split = (shape8 == 1 && fa.tiles_per_wg == 1 && fa.n_sort + 2 * n_fb <= kF8MaxWorkgroups)
                    ? 2 : 1;
     n_fb *= fa.split;
+    if (split3) {
+      fa.ntiles = ceil_div(B, kFsRows);
+      fa.tiles_per_wg = ceil_div(fa.ntiles, kF8MaxWorkgroups);
+      n_fb = ceil_div(fa.ntiles, fa.tiles_per_wg);
+      fa.split = 1;
+    }
     split = fa.split;
     fa.part_stride = ctx->part_stride;
     fa.invB = 1.0f / (float)B;
     {
       Timed tm(ctx, POLYGLOT_K_FWDBWD);
-      if (shape8) {
+      if (split3) {
+        e = launch_step_split(fa, n_fb, tm.L);
+      } else if (shape8) {
         size_t lds = fwdbwd8_lds_bytes(shape8, fa.tiles_per_wg);
         if (fa.n_sort) lds = std::max(lds, part_sort_lds_words(kF8Threads) * 4);
         e = launch_step_fwdbwd8(fa, shape8, fa.n_sort + n_fb, lds, tm.L);

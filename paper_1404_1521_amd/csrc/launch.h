@@ -218,13 +218,19 @@ hipError_t launch_step_fwdbwd(const FwdArgs& a, int NT, int cpw, int grid, size_
 int fwdbwd8_shape(int d, int win, int NT);
 size_t fwdbwd8_lds_bytes(int shape, int tiles_per_wg);
 constexpr int kF8MultiForm = 2;
-// From this many tiles per workgroup the d 64 shape takes the role-specialised
-// form (form 3), whose three-stage pipeline fills and drains over two phases.
-constexpr int kF8WsMinTiles = 8;  // at 4 (B = 16,384) tile pairs were 1 us faster
-constexpr int kF8WsThreads = 12 * kWave;  // its workgroup: 12 waves
 constexpr int kF8Waves = 16;
 constexpr int kF8Threads = kF8Waves * kWave;  // 1024
 constexpr int kF8MaxWorkgroups = 256;         // one workgroup per CU
+// The split form of the d 64 shape (fwdbwd_split_dev.h): 32-window tiles, from
+// this batch on.  Below, its tiles leave most CUs idle and its preparation of
+// W1 weighs more than the tile.  Steps (same box, alternating), float32 tiles
+// against split ones: B = 2048 29.7 against 32.5 us, 3000 33.0, 33.9; 3500
+// 34.4, 34.4; 4096 37.1, 35.6; 8192 44.5, 42.0; 16,384 62.8, 55.1; 32,768 86.9,
+// 75.4; 65,536 128.1, 109.6.
+constexpr int kFsRows = 32;
+constexpr int kFsThreads = 8 * kWave;
+constexpr int kFsMinBatch = 3585;
+hipError_t launch_step_split(const FwdArgs& a, int grid, const Launch& L);
 hipError_t launch_step_fwdbwd8(const FwdArgs& a, int shape, int grid, size_t lds,
                                const Launch& L);
 // First sort launch (whole small sort, or pass-0 tile counts) and, for
