@@ -29,7 +29,10 @@
 // waves: the rest is vector-ALU work (splits, tanh, sums, addresses) that the
 // barriers keep from running under them.  Against the float32 form it replaced
 // (12 waves in roles, 42% of the cycles in matrix instructions at 4 times the
-// number): 71 -> 55 us per launch at B = 65,536, 29 -> 20 us at 16,384.
+// number): 71 -> 55 us per launch at B = 65,536, 29 -> 20 us at 16,384.  The
+// gradients' error against 64 bits (norm of the difference over the norm, six
+// batches of 65,536 and of 4,096): rows of E 6.1e-8 in both forms, W1 6.4e-8 ->
+// 6.1e-8, b1 1.8e-7 -> 1.1e-7, w2 1.1e-7 -> 7e-8.
 #pragma once
 #include "common.h"
 #include "large_dev.h"
@@ -278,13 +281,14 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
                             gw * (1.f - ht[n] * ht[n])};
 #pragma unroll
         for (int y = 0; y < 3; ++y) {
-          float r = v[y];
-#pragma unroll
-          for (int p = 0; p < 3; ++p) {
-            const uint32_t b = __float_as_uint(r);
-            vt[((y * 2 + n) * 3 + p) * 2 * kWave * 4] = (uint16_t)(b >> 16);
-            r -= __uint_as_float(b & 0xffff0000u);
-          }
+          const uint32_t u = __float_as_uint(v[y]);
+          const float r = v[y] - __uint_as_float(u & 0xffff0000u);
+          const uint32_t mm = lg_round2(r, r);
+          const float q3 = r - __uint_as_float(mm << 16);
+          uint16_t* d = vt + (y * 2 + n) * 3 * 2 * kWave * 4;
+          d[0] = (uint16_t)(u >> 16);
+          d[2 * kWave * 4] = (uint16_t)mm;
+          d[2 * 2 * kWave * 4] = (uint16_t)(__float_as_uint(q3) >> 16);
         }
         db1a[n] += v[0];
         dw2a[n] -= gst * hmh[n];  // -(m/B) h + (m/B) h~
