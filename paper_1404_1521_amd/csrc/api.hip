@@ -443,7 +443,7 @@ int enqueue_compute(polyglot_ctx* ctx, float* E, float* W1, float* b1, float* w2
     aa.dn.kx = cf.d;
     aa.dn.c0 = ctx->c * cf.d;
     aa.dn.vpart = ctx->ws.vpart;
-    aa.dn.n_vparts = large_fwd_grid(B);
+    aa.dn.n_vparts = large_fwd_grid(B, cf.H);
     aa.dn.vstride = 2 * cf.H + 2;
   } else {
     aa.dn.n_parts = n_fb;
@@ -642,10 +642,10 @@ int polyglot_init(const polyglot_config* cfg, void* stream, polyglot_ctx** out) 
   }
   if (e == hipSuccess) e = alloc(ctx, &ws.G, (size_t)c.max_batch * (c.win + 1) * c.d);
   if (large) {
-    // at most one forward workgroup per CU, or one per 64 windows
+    // at most one forward workgroup per CU, or one per 32 windows
     const int slices = large_dw1_max_slices(c.H, c.d, c.win, c.max_batch);
     const int fwd_wgs = std::min(ceil_div(c.max_batch, 16),
-                                 std::max(kCus, ceil_div(c.max_batch, 64)));
+                                 std::max(kCus, ceil_div(c.max_batch, 32)));
     // one block: W1's fragments (2 layouts x 6 bytes), V, the dW1 slices (all
     // multiples of 16 bytes), then the forward's partials
     const size_t n_wf = (size_t)c.H * ctx->K * 3, n_v = (size_t)c.max_batch * 3 * c.H;

@@ -90,13 +90,13 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
   const int ntl = min(a.tiles_per_wg, a.ntiles - tile0);  // tiles of this workgroup (>= 1)
 
   // ids of a tile: thread t < 192 takes entry t (row t / 6, position t % 6)
-  auto load_id = [&](int tile) {
+  auto load_id = [&](int tile) LG_INLINE {
     const int r = t / W1P, j = t - r * W1P, b = tile * R + r;
     int32_t id = 0;
     if (t < R * W1P && b < a.B) id = j < Sh::WIN ? a.windows[(size_t)b * Sh::WIN + j] : a.corrupt[b];
     return id;
   };
-  auto store_id = [&](int buf, int32_t id) {  // rows >= B and bad ids read row 0
+  auto store_id = [&](int buf, int32_t id) LG_INLINE {  // rows >= B and bad ids read row 0
     const bool bad = (uint32_t)id >= (uint32_t)a.V;
     if (bad) atomicOr(a.flag, kFlagBadId);
     if (t < R * W1P) idt[buf * R * W1P + t] = bad ? 0 : id;
@@ -104,7 +104,7 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
   // unit u = t + 512 v of a tile's rows: row 16 (u / 64 % 2) + u % 16, column
   // step u / 128 (position u / 256), columns 8 (u / 16 % 4) of it
   f4 xr[3][2];
-  auto load_x = [&](int buf) {
+  auto load_x = [&](int buf) LG_INLINE {
 #pragma unroll
     for (int v = 0; v < 3; ++v) {
       const int u = t + v * NT, ks = u >> 7;
@@ -115,7 +115,7 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
     }
   };
   lu4 xp[3][3];
-  auto split_x = [&]() {
+  auto split_x = [&]() LG_INLINE {
 #pragma unroll
     for (int v = 0; v < 3; ++v) {
       float x[8];
@@ -124,7 +124,7 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
       lg_split8(x, xp[v]);
     }
   };
-  auto store_x = [&]() {
+  auto store_x = [&]() LG_INLINE {
 #pragma unroll
     for (int v = 0; v < 3; ++v)
 #pragma unroll

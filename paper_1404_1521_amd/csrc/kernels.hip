@@ -392,12 +392,12 @@ hipError_t launch_large_prep(const LargeArgs& a, const Launch& L) {
 
 template <int NW, bool SCORE>
 static hipError_t launch_large_fwd_t(const LargeArgs& a, const Launch& L) {
-  const dim3 grid(large_fwd_grid(a.B)), block(NW * kWave);
-  switch (large_fwd_mt(a.B)) {
-    case 1: return pg_launch(k_large_fwd<NW, 1, SCORE>, grid, block, 0, L, a);
-    case 2: return pg_launch(k_large_fwd<NW, 2, SCORE>, grid, block, 0, L, a);
-    default: return pg_launch(k_large_fwd<NW, 4, SCORE>, grid, block, 0, L, a);
-  }
+  const dim3 grid(large_fwd_grid(a.B, a.H)), block(NW * kWave);
+  const int mt = large_fwd_mt(a.B, a.H);
+  if (mt == 1) return pg_launch(k_large_fwd<NW, 1, SCORE>, grid, block, 0, L, a);
+  if constexpr (NW != 6)
+    if (mt == 4) return pg_launch(k_large_fwd<NW, 4, SCORE>, grid, block, 0, L, a);
+  return pg_launch(k_large_fwd<NW, 2, SCORE>, grid, block, 0, L, a);
 }
 
 hipError_t launch_large_fwd(const LargeArgs& a, int score_only, const Launch& L) {

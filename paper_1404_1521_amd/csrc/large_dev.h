@@ -44,6 +44,10 @@
 
 namespace pg {
 
+// On the kernels' lambdas: one that is called from several places and not
+// inlined takes the arrays it captures to scratch memory.
+#define LG_INLINE __attribute__((always_inline))
+
 typedef __bf16 lb8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ f4 lg_mfma(lu4 a, lu4 b, f4 c) {
@@ -217,12 +221,12 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
 
   const int dch = d / 64, nch = a.K / 64, hb = a.H / 16;
   // chunk q in the order of work: the centre block's, then the others
-  auto chunk_of = [&](int q) {
+  auto chunk_of = [&](int q) LG_INLINE {
     return q < dch ? a.c * dch + q : (q < (a.c + 1) * dch ? q - dch : q);
   };
   f4 X[UPT][2], C[UPT][2];
   // unit u of a chunk: row 16 (u / 128) + (u & 15), columns 32 ks + 8 g ..
-  auto load = [&](int q) {
+  auto load = [&](int q) LG_INLINE {
     const int kc = chunk_of(q), jb = kc / dch, off = (kc - jb * dch) * 64;
 #pragma unroll
     for (int v = 0; v < UPT; ++v) {
@@ -240,7 +244,7 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
       }
     }
   };
-  auto store = [&](auto centre, int buf) {
+  auto store = [&](auto centre, int buf) LG_INLINE {
 #pragma unroll
     for (int v = 0; v < UPT; ++v) {
       const int u = t + v * NT;
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
       }
     }
   };
-  auto load_w = [&](int q, int ks, lu4 (&Bv)[2][3]) {
+  auto load_w = [&](int q, int ks, lu4 (&Bv)[2][3]) LG_INLINE {
     const lu4* src = a.wf + ((size_t)(2 * chunk_of(q) + ks) * hb + 2 * w) * 3 * kWave + lane;
 #pragma unroll
     for (int n = 0; n < 2; ++n)
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
 #pragma unroll
     for (int n = 0; n < 2; ++n) dh[m][n] = dl[m][n] = kZero4;
   // the next chunk's rows into the other buffer, the one after that into registers
-  auto stage = [&](int q) {
+  auto stage = [&](int q) LG_INLINE {
     if (q + 1 < nch) {
       if (!SCORE && q + 1 < dch) store(std::true_type{}, (q + 1) & 1);
       else store(std::false_type{}, (q + 1) & 1);
@@ -297,7 +301,7 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
   __syncthreads();
   // chunk q, in buffer q & 1: one barrier each.  The two waves of a SIMD stage
   // at opposite ends of the chunk, so that one splits while the other multiplies.
-  auto chunk = [&](auto centre, int q) {
+  auto chunk = [&](auto centre, int q) LG_INLINE {
     const int buf = q & 1;
     if (w < NW / 2) stage(q);
     const int qn = min(q + 1, nch - 1);  // (the last chunk's own again: not used)
@@ -492,7 +496,7 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
 
   const float* vbase = a.V + (size_t)b_lo * 3 * H + (size_t)ty * H;
   float vr[VU][8], xr[XU][8];
-  auto load_t = [&](auto tail, int st) {  // tail: the step has windows past the slice
+  auto load_t = [&](auto tail, int st) LG_INLINE {  // tail: the step has windows past the slice
     constexpr bool TAIL = decltype(tail)::value;
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
@@ -516,11 +520,11 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
       }
     }
   };
-  auto load = [&](int st) {
+  auto load = [&](int st) LG_INLINE {
     if (32 * st + 32 <= nb) load_t(std::false_type{}, st);
     else load_t(std::true_type{}, st);
   };
-  auto store = [&](int buf) {
+  auto store = [&](int buf) LG_INLINE {
     lu4 p[3];
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
@@ -553,7 +557,7 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
   // step st reads buffer st & 1 and fills the other one, last read at step
   // st - 1, before its closing barrier.  The two waves of a SIMD stage at
   // opposite ends of the step, so that one splits while the other multiplies.
-  auto stage = [&](int st) {
+  auto stage = [&](int st) LG_INLINE {
     if (st + 1 < steps) store((st + 1) & 1);
     if (st + 2 < steps) load(st + 2);
   };
@@ -564,7 +568,7 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
     const lu4* xs = Xs + buf * XF + wc * 4 * 3 * kWave + lane;
     lu4 A[4][3], Bv[2][3];
     lg_read<4>(vs, A);
-    auto read_b = [&](int n, lu4 (&Bn)[3]) {
+    auto read_b = [&](int n, lu4 (&Bn)[3]) LG_INLINE {
 #pragma unroll
       for (int k = 0; k < 3; ++k) Bn[k] = xs[(n * 3 + k) * kWave];
     };
@@ -625,7 +629,7 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
 
   // unit u: windows 16 (u / 64 % 4) + (u & 15), hidden units 8g.. of step u / 256
   f4 vr[UPT][2];
-  auto load = [&](int ty) {
+  auto load = [&](int ty) LG_INLINE {
 #pragma unroll
     for (int v = 0; v < UPT; ++v) {
       const int u = t + v * NT, s = u >> 6;
@@ -638,7 +642,7 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
       }
     }
   };
-  auto store = [&]() {
+  auto store = [&]() LG_INLINE {
 #pragma unroll
     for (int v = 0; v < UPT; ++v) {
       const int u = t + v * NT, s = u >> 6;
@@ -653,7 +657,7 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
       }
     }
   };
-  auto load_w = [&](int jj, int hs, lu4 (&Bv)[2][3]) {
+  auto load_w = [&](int jj, int hs, lu4 (&Bv)[2][3]) LG_INLINE {
     const lu4* src = a.wg + ((size_t)(jj * (D / 16) + 2 * cg) * ns + hs) * 3 * kWave + lane;
 #pragma unroll
     for (int n = 0; n < 2; ++n)
@@ -661,12 +665,12 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
       for (int k = 0; k < 3; ++k) Bv[n][k] = src[((size_t)n * ns * 3 + k) * kWave];
   };
   // position o of the order: entry position and W1 block
-  auto entry = [&](int o) { return o < nctx ? o + (o >= a.c) : (o == nctx ? a.c : a.win); };
-  auto block = [&](int o) { return o < nctx ? o + (o >= a.c) : a.c; };
+  auto entry = [&](int o) LG_INLINE { return o < nctx ? o + (o >= a.c) : (o == nctx ? a.c : a.win); };
+  auto block = [&](int o) LG_INLINE { return o < nctx ? o + (o >= a.c) : a.c; };
   lu4 B0[2][3], B1[2][3];
   // output rows [16 m0, 16 (m0 + MT)) of position o, whose first two steps'
   // fragments are loaded; loads those of position on (if >= 0) at the end
-  auto compute = [&](auto mt_c, int m0, int o, int on) {
+  auto compute = [&](auto mt_c, int m0, int o, int on) LG_INLINE {
     constexpr int MT = decltype(mt_c)::value;
     f4 hi[MT][2], lo[MT][2];
 #pragma unroll
@@ -674,7 +678,7 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
 #pragma unroll
       for (int n = 0; n < 2; ++n) hi[m][n] = lo[m][n] = kZero4;
     const int jj = block(o), jn = on >= 0 ? block(on) : -1;
-    auto step = [&](int hs, lu4 (&Bv)[2][3]) {
+    auto step = [&](int hs, lu4 (&Bv)[2][3]) LG_INLINE {
       lg_step<MT>(lds_q + (hs * 4 + m0) * 3 * kWave + lane, Bv, hi, lo);
       if (hs + 2 < ns) load_w(jj, hs + 2, Bv);
       else if (jn >= 0) load_w(jn, hs + 2 - ns, Bv);
@@ -701,11 +705,11 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
   const int whole = o_lo < c_hi ? (c_hi - o_lo) / PG * PG : 0;  // positions taken whole
   const int o_s = o_lo + whole;                                 // first one split by windows
   // this wave's positions in order: o_lo + pg, + PG, ... below o_s, then o_s .. o_hi - 1
-  auto next_of = [&](int o) {
+  auto next_of = [&](int o) LG_INLINE {
     const int nx = o < o_s ? (o + PG < o_s ? o + PG : o_s) : o + 1;
     return nx < o_hi ? nx : -1;
   };
-  auto type_of = [&](int o) { return o < nctx ? 0 : (o == nctx ? 1 : 2); };
+  auto type_of = [&](int o) LG_INLINE { return o < nctx ? 0 : (o == nctx ? 1 : 2); };
   int o = whole > 0 ? o_lo + pg : o_s;
   load_w(block(o), 0, B0);
   load_w(block(o), 1, B1);

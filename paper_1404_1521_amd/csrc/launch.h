@@ -69,11 +69,12 @@ constexpr int kLgGRows = 64;       // windows per G workgroup
 
 // 16-window tiles per forward workgroup: the fewest (1, 2 or 4) that need at
 // most one workgroup per CU, so that small batches spread over the chip;
-// larger ones reread W1 less.
-inline int large_fwd_mt(int B) {
-  return B <= 16 * kCus ? 1 : (B <= 32 * kCus ? 2 : 4);
+// larger ones reread W1 less.  (192 hidden units stop at 2: six waves stage 64
+// rows in two uneven rounds, and their registers spill at 4.)
+inline int large_fwd_mt(int B, int H) {
+  return B <= 16 * kCus ? 1 : (B <= 32 * kCus || H == 192 ? 2 : 4);
 }
-inline int large_fwd_grid(int B) { return ceil_div(B, 16 * large_fwd_mt(B)); }
+inline int large_fwd_grid(int B, int H) { return ceil_div(B, 16 * large_fwd_mt(B, H)); }
 
 // Columns of a dW1 workgroup: 128 when they stay inside one window position.
 inline int large_dw1_cols(int d) { return d % 128 == 0 ? 128 : 64; }
