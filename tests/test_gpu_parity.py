@@ -559,11 +559,10 @@ def test_update_forms_at_their_limits(B):
 
 @pytest.mark.parametrize("B", [4100, 8215, 8231])
 def test_pipelined_tiles_ragged(B):
-    """More than 256 tiles, so workgroups take their tiles in pairs (an even
-    number per workgroup), and the last workgroup fewer: 257 tiles at two per
-    workgroup (the last has one: a pair whose second tile is past the batch),
-    514 and 515 tiles at four per workgroup (the last has two or three); the
-    last tile holds 4, 7 or 7 windows."""
+    """Batches of the 32-window tiles: 129 tiles at one per workgroup, 257 and
+    258 at two (the last workgroup has one or both); the last tile holds 4, 23
+    or 7 windows.  (Cut into 16-window tiles, as the asserts count them, they
+    fill no even share per workgroup either.)"""
     ntiles = -(-B // 16)
     per = -(-ntiles // 256)
     per += per & 1
@@ -574,17 +573,26 @@ def test_pipelined_tiles_ragged(B):
 
 @pytest.mark.parametrize("B", [32653, 32773])
 def test_role_specialised_tiles_ragged(B):
-    """Eight or more tiles per workgroup take the role-specialised form
-    (staging, forward and dW1 waves pipelined one tile apart): 2041 tiles at
-    eight per workgroup leave the last workgroup one tile (the pipeline's
-    fill and drain with nothing between), 2049 tiles at ten per workgroup
-    leave it nine; the last tile holds 13 or 5 windows."""
+    """Large batches of the 32-window tiles: 1021 tiles at four per workgroup
+    leave the last workgroup one tile, 1025 at five leave it all; the last
+    tile holds 13 or 5 windows."""
     ntiles = -(-B // 16)
     per = -(-ntiles // 256)
     per += per & 1
     assert per >= 8 and ntiles % per in (1, 9) and B % 16 != 0
     w = PRESETS["sweep_1024"].with_batch(B)
     run_both(w, 2, B, 0)
+
+
+# Both sides of the switch to 32-window tiles (3,585 windows), hidden layers that
+# leave padding rows, a last tile of one window, the atomic update; and the d 16
+# shape's tile pairs, the last workgroup with one tile.
+@pytest.mark.parametrize("d,H,B,mode", [(64, 32, 3584, 0), (64, 32, 3585, 0), (64, 17, 3585, 1),
+                                        (64, 25, 8193, 0), (64, 31, 16_417, 0), (16, 8, 4100, 0)])
+def test_split_tiles_at_their_limits(d, H, B, mode):
+    w = workloads.Workload(f"w5_d{d}_h{H}", V=20_000, d=d, win=5, H=H, B=B, lr=0.5, steps=2,
+                           zipf_s=1.0, seed=31)
+    run_both(w, 2, B, mode)
 
 
 @pytest.mark.parametrize("mode", [0, 1])
