@@ -108,7 +108,8 @@ def step_model(w, B, st, passes, n_parts):
     fwdbwd: ids and rows read, W1 read, the per-window vectors (3H floats)
       and the db1/dw2/loss partials written; flops 2HK + 2Hd per window.
     wide_dw1: ids and rows read, the per-window vectors read, one dW1
-      partial per 1024-window slice written; flops 2HK + 2Hd per window.
+      partial per 1024 windows written (the kernel sizes its slices by the
+      batch); flops 2HK + 2Hd per window.
     wide_g: the per-window vectors and W1 read, G written; flops
       (win+1) 2Hd per window.
     sort: 16 B per entry per radix pass (keys and values, read and written).
