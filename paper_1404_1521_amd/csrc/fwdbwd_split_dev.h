@@ -25,8 +25,8 @@
 //   S  the split rows go to LDS
 // Timestamps at B = 65,536 (8 tiles per workgroup, cycles at about 2.1 GHz): W1
 // and the first rows 10,400, then per tile F 4,300, E 2,200, B 5,500, S 1,100.
-// The 144 matrix instructions of a wave take 4,600 of them on a SIMD of two
-// waves: the rest is vector-ALU work (splits, tanh, sums, addresses) that the
+// The 108 matrix instructions of a wave take 3,460 of them on a SIMD of two
+// waves (counters: 19% of a launch): the rest is vector-ALU work (splits, tanh, sums, addresses) that the
 // barriers keep from running under them.  Against the float32 form it replaced
 // (12 waves in roles, 42% of the cycles in matrix instructions at 4 times the
 // number): 71 -> 55 us per launch at B = 65,536, 29 -> 20 us at 16,384.  The
