@@ -116,13 +116,17 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
   };
   lu4 xp[3][3];
   auto split_x = [&]() LG_INLINE {
+    float x[3][8], big = 0.f;
 #pragma unroll
     for (int v = 0; v < 3; ++v) {
-      float x[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = xr[v][e >> 2][e & 3];
-      lg_split8(x, xp[v]);
+      for (int e = 0; e < 8; ++e) x[v][e] = xr[v][e >> 2][e & 3];
+      lg_largest(x[v], big);
     }
+    lg_checked(big, [&](auto safe) LG_INLINE {
+#pragma unroll
+      for (int v = 0; v < 3; ++v) lg_split8<decltype(safe)::value>(x[v], xp[v]);
+    });
   };
   auto store_x = [&]() LG_INLINE {
 #pragma unroll
@@ -144,17 +148,16 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
   const int xu[3] = {kq == 0 ? 0 : (kq == 1 ? 3 : (kq == 2 ? 6 : 7)),
                      kq == 0 ? 1 : (kq == 1 ? 4 : (kq == 2 ? 5 : 8)),
                      kq == 0 ? 2 : (kq == 1 ? 10 : (kq == 2 ? 11 : 9))};
-  lu4 wf[3][3];
+  float wx[6][8], wbig = 0.f;  // the forward's three units, then G's three blocks
 #pragma unroll
   for (int u = 0; u < 3; ++u) {
     const int ks = xu[u] >= 2 * Sh::WIN ? xu[u] - 2 * (Sh::WIN - C) : xu[u];
     const int n = 16 * nf + i;
     const float* src = a.W1 + (size_t)(n < a.H ? n : 0) * K + 32 * ks + 8 * g;
     const f4 v0 = ld4(src), v1 = ld4(src + 4);
-    float x[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = n < a.H ? (e < 4 ? v0[e & 3] : v1[e & 3]) : 0.f;
-    lg_split8(x, wf[u]);
+    for (int e = 0; e < 8; ++e) wx[u][e] = n < a.H ? (e < 4 ? v0[e & 3] : v1[e & 3]) : 0.f;
+    lg_largest(wx[u], wbig);
   }
   // the backward's blocks: block 3w + u of the 24 (position pu, 16 columns at
   // 16 cq) ordered true centre, corrupt, contexts, so that most waves need one
@@ -167,19 +170,24 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
     pu[u] = o == 0 ? C : (o == 1 ? Sh::WIN : (o < 4 ? o - 2 : o - 1));
     ty[u] = o == 0 ? 1 : (o == 1 ? 2 : 0);
   }
-  lu4 wg3[3][3];  // lane (i, g): W1[4g .. 4g + 3 and 16 + 4g ..][column i]
+  lu4 wf[3][3], wg3[3][3];  // wg3, lane (i, g): W1[4g .. 4g + 3 and 16 + 4g ..][column i]
 #pragma unroll
   for (int u = 0; u < 3; ++u) {
     const int blk = pu[u] == Sh::WIN ? C : pu[u];
-    float x[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int h = 16 * (e >> 2) + 4 * g + (e & 3);
-      x[e] = a.W1[(size_t)(h < a.H ? h : 0) * K + blk * D + 16 * cq[u] + i];
-      x[e] = h < a.H ? x[e] : 0.f;
+      const float x = a.W1[(size_t)(h < a.H ? h : 0) * K + blk * D + 16 * cq[u] + i];
+      wx[3 + u][e] = h < a.H ? x : 0.f;
     }
-    lg_split8(x, wg3[u]);
+    lg_largest(wx[3 + u], wbig);
   }
+  lg_checked(wbig, [&](auto safe) LG_INLINE {
+#pragma unroll
+    for (int u = 0; u < 3; ++u) lg_split8<decltype(safe)::value>(wx[u], wf[u]);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) lg_split8<decltype(safe)::value>(wx[3 + u], wg3[u]);
+  });
   float b1v[2], w2v[2];
 #pragma unroll
   for (int n = 0; n < 2; ++n) {
@@ -274,25 +282,32 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
       const bool on = row < a.B && mg > 0.f;  // hinge active (derivative 0 at margin 0)
       const float gst = on ? a.invB : 0.f;    // d loss/d s~ = m/B, d loss/d s = -m/B
       uint16_t* vt = reinterpret_cast<uint16_t*>(vs) + (m * kWave + lane) * 4 + q;
+      float v[2][3], big = 0.f;
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
         const float gw = gst * w2v[n];
-        const float v[3] = {gw * hmh[n] * (h[n] + ht[n]), -gw * (1.f - h[n] * h[n]),
-                            gw * (1.f - ht[n] * ht[n])};
-#pragma unroll
-        for (int y = 0; y < 3; ++y) {
-          const uint32_t u = __float_as_uint(v[y]);
-          const float r = v[y] - __uint_as_float(u & 0xffff0000u);
-          const uint32_t mm = lg_round2(r, r);
-          const float q3 = r - __uint_as_float(mm << 16);
-          uint16_t* d = vt + (y * 2 + n) * 3 * 2 * kWave * 4;
-          d[0] = (uint16_t)(u >> 16);
-          d[2 * kWave * 4] = (uint16_t)mm;
-          d[2 * 2 * kWave * 4] = (uint16_t)(__float_as_uint(q3) >> 16);
-        }
-        db1a[n] += v[0];
+        v[n][0] = gw * hmh[n] * (h[n] + ht[n]);
+        v[n][1] = -gw * (1.f - h[n] * h[n]);
+        v[n][2] = gw * (1.f - ht[n] * ht[n]);
+        lg_largest(v[n], big);
+        db1a[n] += v[n][0];
         dw2a[n] -= gst * hmh[n];  // -(m/B) h + (m/B) h~
       }
+      lg_checked(big, [&](auto safe) LG_INLINE {
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+          for (int y = 0; y < 3; ++y) {
+            const uint32_t u = lg_first2<decltype(safe)::value>(v[n][y], v[n][y]);
+            const float r = v[n][y] - __uint_as_float(u << 16);
+            const uint32_t mm = lg_round2(r, r);
+            const float q3 = r - __uint_as_float(mm << 16);
+            uint16_t* d = vt + (y * 2 + n) * 3 * 2 * kWave * 4;
+            d[0] = (uint16_t)u;
+            d[2 * kWave * 4] = (uint16_t)mm;
+            d[2 * 2 * kWave * 4] = (uint16_t)(__float_as_uint(q3) >> 16);
+          }
+      });
       if (i == 0) lossa += on ? mg : 0.f;
     }
     store_id(tt & 1, idn);

@@ -20,22 +20,26 @@
 //                 through block c).
 // Rows b >= B read row 0 (or zero) and are masked out of every result.
 //
-// The split.  x = x1 + x2 + x3, each term 8 significant bits of what is left:
-// x1 truncated, so that it cannot overflow; x2 rounded to nearest, so that x3
-// and with it what is dropped has no preferred sign; the three hold all 24
-// bits.  Of the nine products the six of weight 2^-16 and more are kept; the
-// others are below 2^-25 of the product, half a float32 rounding.  x1 y1 goes to an
-// accumulator of its own and the other five to a second one, so a contraction
-// rounds at the size of its sum once per 32 terms, where the float32
-// instruction rounds once per 4: against 64 bits the error of a 1408-term
-// contraction is 2.2e-7 of the result's norm, that of the float32 instruction
-// 6.7e-7 (320 terms: 1.0e-7 and 3.2e-7).  An infinite operand has finite
-// companions no more (inf - inf), which only the second accumulator sees: a
-// non-finite first sum is the result, as one float32 chain would give it.
+// The split.  x = x1 + x2 + x3, each term what is left rounded to 8 significant
+// bits; the three hold all 24.  Rounding to nearest keeps x2 within 2^-8 of x's
+// leading bit and x3 within 2^-17, and without a preferred sign.  Of the nine
+// products six are kept; the others (x2 y3, x3 y2, x3 y3) are below 2^-24 of the
+// product, a float32 rounding, and 2^-27.4 in the root mean square (normal
+// operands; truncating x1 instead left 2^-22.0 and 2^-25.4, the former with one
+// sign where entries repeat).  An operand below 2^-110 keeps what lies above
+// 2^-133, the smallest bfloat16.  x1 y1 goes to an accumulator of its own and the
+// other five to a second one, so a contraction rounds at the size of its sum once
+// per 32 terms, where the float32 instruction rounds once per 4: the largest error
+// of 256 random terms over the sum of their magnitudes is 0.8 x 2^-24, that of the
+// float32 instruction 3.6 x 2^-24; of 256 equal ones 1.3 and 2.6.
+// An infinite operand has finite companions no more (inf - inf), which only the
+// second accumulator sees: a non-finite first sum is the result, as one float32
+// chain would give it.
 // Six bfloat16 products take 96 matrix cycles per 16x16x32 block, eight
 // float32 ones 256.  Gradients of the d 128, window 11, H 256 model at B =
-// 16,384, error against 64 bits, float32 instructions -> this: rows of E 7.9e-8
-// -> 6.5e-8, W1 2.6e-7 -> 6.1e-8, b1 3.4e-7 -> 1.6e-7.
+// 16,384, error against 64 bits (norm of the difference over the norm, six
+// batches), float32 instructions -> this: rows of E 7.6e-8 -> 6.1e-8, W1 2.6e-7
+// -> 5.9e-8, b1 3.4e-7 -> 1.6e-7, w2 8.3e-8 -> 6.2e-8.
 #pragma once
 #include <type_traits>
 
@@ -62,14 +66,38 @@ __device__ __forceinline__ uint32_t lg_round2(float x, float y) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x, y}, b2));
 }
 
+// Finite floats above the largest bfloat16 round to an infinity; as first terms
+// they are truncated to it (the second term holds the rest).  Callers look for
+// them once for all that a phase splits, and take its SAFE copy if one is there.
+constexpr float kLgMax = 0x1.fep127f;
+template <int N>
+__device__ __forceinline__ void lg_largest(const float (&x)[N], float& big) {
+#pragma unroll
+  for (int e = 0; e < N; ++e) big = __builtin_elementwise_maximum(big, __builtin_fabsf(x[e]));
+}
+// f(std::true_type) if a lane of the wave has such a value (or an infinity, or a
+// NaN, which would hide one), else f(std::false_type).
+template <class F>
+__device__ __forceinline__ void lg_checked(float big, F f) {
+  if (__builtin_expect(__ballot(!(big <= kLgMax)) != 0, 0)) f(std::true_type{});
+  else f(std::false_type{});
+}
+template <bool SAFE>
+__device__ __forceinline__ uint32_t lg_first2(float x, float y) {
+  if (SAFE && __builtin_fabsf(x) < __builtin_inff()) x = __builtin_amdgcn_fmed3f(x, -kLgMax, kLgMax);
+  if (SAFE && __builtin_fabsf(y) < __builtin_inff()) y = __builtin_amdgcn_fmed3f(y, -kLgMax, kLgMax);
+  return lg_round2(x, y);
+}
+
 // The three bfloat16 terms of eight floats, packed in order.
+template <bool SAFE>
 __device__ __forceinline__ void lg_split8(const float (&x)[8], lu4 (&p)[3]) {
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const uint32_t u0 = __float_as_uint(x[2 * v]), u1 = __float_as_uint(x[2 * v + 1]);
-    p[0][v] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // both upper halves
-    float r0 = x[2 * v] - __uint_as_float(u0 & 0xffff0000u);
-    float r1 = x[2 * v + 1] - __uint_as_float(u1 & 0xffff0000u);
+    const uint32_t u = lg_first2<SAFE>(x[2 * v], x[2 * v + 1]);
+    p[0][v] = u;
+    float r0 = x[2 * v] - __uint_as_float(u << 16);
+    float r1 = x[2 * v + 1] - __uint_as_float(u & 0xffff0000u);
     const uint32_t m = lg_round2(r0, r1);
     p[1][v] = m;
     r0 -= __uint_as_float(m << 16);
@@ -164,10 +192,14 @@ __global__ __launch_bounds__(kBlock) void k_large_prep(LargeArgs a) {
     for (int e = 0; e < 8; ++e) x[e] = src[(size_t)e * a.K];
     dst = a.wg + (size_t)u * 3 * kWave;
   }
-  lu4 p[3];
-  lg_split8(x, p);
+  float big = 0.f;
+  lg_largest(x, big);
+  lg_checked(big, [&](auto safe) LG_INLINE {
+    lu4 p[3];
+    lg_split8<decltype(safe)::value>(x, p);
 #pragma unroll
-  for (int k = 0; k < 3; ++k) dst[k * kWave + lane] = p[k];
+    for (int k = 0; k < 3; ++k) dst[k * kWave + lane] = p[k];
+  });
 }
 
 // =============================================================== forward
@@ -245,27 +277,39 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
     }
   };
   auto store = [&](auto centre, int buf) LG_INLINE {
+    constexpr bool CTR = decltype(centre)::value;
+    float x[UPT][8], dx[UPT][8], big = 0.f;
 #pragma unroll
     for (int v = 0; v < UPT; ++v) {
-      const int u = t + v * NT;
-      if (UN % NT == 0 || u < UN) {
-        const int slot = (((u >> 6) & 1) * MT + (u >> 7)) * 3 * kWave + (u & 63);
-        float x[8];
-        lu4 p[3];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = X[v][e >> 2][e & 3];
-        lg_split8(x, p);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) Xs[buf][slot + k * kWave] = p[k];
-        if constexpr (decltype(centre)::value) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) x[e] = C[v][e >> 2][e & 3] - x[e];
-          lg_split8(x, p);
-#pragma unroll
-          for (int k = 0; k < 3; ++k) Ts[buf][slot + k * kWave] = p[k];
-        }
+      for (int e = 0; e < 8; ++e) {
+        x[v][e] = X[v][e >> 2][e & 3];
+        if (CTR) dx[v][e] = C[v][e >> 2][e & 3] - x[v][e];
+      }
+      if (UN % NT == 0 || t + v * NT < UN) {
+        lg_largest(x[v], big);
+        if (CTR) lg_largest(dx[v], big);
       }
     }
+    lg_checked(big, [&](auto safe) LG_INLINE {
+      constexpr bool SAFE = decltype(safe)::value;
+#pragma unroll
+      for (int v = 0; v < UPT; ++v) {
+        const int u = t + v * NT;
+        if (UN % NT == 0 || u < UN) {
+          const int slot = (((u >> 6) & 1) * MT + (u >> 7)) * 3 * kWave + (u & 63);
+          lu4 p[3];
+          lg_split8<SAFE>(x[v], p);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) Xs[buf][slot + k * kWave] = p[k];
+          if constexpr (CTR) {
+            lg_split8<SAFE>(dx[v], p);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) Ts[buf][slot + k * kWave] = p[k];
+          }
+        }
+      }
+    });
   };
   auto load_w = [&](int q, int ks, lu4 (&Bv)[2][3]) LG_INLINE {
     const lu4* src = a.wf + ((size_t)(2 * chunk_of(q) + ks) * hb + 2 * w) * 3 * kWave + lane;
@@ -525,25 +569,34 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
     else load_t(std::true_type{}, st);
   };
   auto store = [&](int buf) LG_INLINE {
-    lu4 p[3];
+    float big = 0.f;
 #pragma unroll
-    for (int u = 0; u < VU; ++u) {
-      const int x = t + u * NT, h = x % H, gq = x / H;
-      lg_split8(vr[u], p);
+    for (int u = 0; u < VU; ++u) lg_largest(vr[u], big);
 #pragma unroll
-      for (int k = 0; k < 3; ++k)
-        Vs[buf * VF + ((h >> 4) * 3 + k) * kWave + 16 * gq + (h & 15)] = p[k];
-    }
+    for (int u = 0; u < XU; ++u)
+      if (CB * 4 % NT == 0 || t + u * NT < CB * 4) lg_largest(xr[u], big);
+    lg_checked(big, [&](auto safe) LG_INLINE {
+      constexpr bool SAFE = decltype(safe)::value;
+      lu4 p[3];
 #pragma unroll
-    for (int u = 0; u < XU; ++u) {
-      const int x = t + u * NT, col = x % CB, gq = x / CB;
-      if (CB * 4 % NT == 0 || x < CB * 4) {
-        lg_split8(xr[u], p);
+      for (int u = 0; u < VU; ++u) {
+        const int x = t + u * NT, h = x % H, gq = x / H;
+        lg_split8<SAFE>(vr[u], p);
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-          Xs[buf * XF + ((col >> 4) * 3 + k) * kWave + 16 * gq + (col & 15)] = p[k];
+          Vs[buf * VF + ((h >> 4) * 3 + k) * kWave + 16 * gq + (h & 15)] = p[k];
       }
-    }
+#pragma unroll
+      for (int u = 0; u < XU; ++u) {
+        const int x = t + u * NT, col = x % CB, gq = x / CB;
+        if (CB * 4 % NT == 0 || x < CB * 4) {
+          lg_split8<SAFE>(xr[u], p);
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+            Xs[buf * XF + ((col >> 4) * 3 + k) * kWave + 16 * gq + (col & 15)] = p[k];
+        }
+      }
+    });
   };
   f4 hi[4][4], lo[4][4];
 #pragma unroll
@@ -643,19 +696,29 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
     }
   };
   auto store = [&]() LG_INLINE {
+    float big = 0.f;
 #pragma unroll
-    for (int v = 0; v < UPT; ++v) {
-      const int u = t + v * NT, s = u >> 6;
-      if (s < 4 * ns) {
-        float x[8];
-        lu4 p[3];
+    for (int v = 0; v < UPT; ++v)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = vr[v][e >> 2][e & 3];
-        lg_split8(x, p);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) lds_q[(s * 3 + k) * kWave + (u & 63)] = p[k];
+      for (int k = 0; k < 2; ++k) {
+        const float x[4] = {vr[v][k][0], vr[v][k][1], vr[v][k][2], vr[v][k][3]};
+        lg_largest(x, big);
       }
-    }
+    lg_checked(big, [&](auto safe) LG_INLINE {
+#pragma unroll
+      for (int v = 0; v < UPT; ++v) {
+        const int u = t + v * NT, s = u >> 6;
+        if (s < 4 * ns) {
+          float x[8];
+          lu4 p[3];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[e] = vr[v][e >> 2][e & 3];
+          lg_split8<decltype(safe)::value>(x, p);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) lds_q[(s * 3 + k) * kWave + (u & 63)] = p[k];
+        }
+      }
+    });
   };
   auto load_w = [&](int jj, int hs, lu4 (&Bv)[2][3]) LG_INLINE {
     const lu4* src = a.wg + ((size_t)(jj * (D / 16) + 2 * cg) * ns + hs) * 3 * kWave + lane;

@@ -678,6 +678,156 @@ def test_wide_scores_of_infinite_rows():
     np.testing.assert_allclose(got[~nan], oracle.score(p, ids)[~nan], rtol=1e-5, atol=1e-6)
 
 
+# ---------------------------------------------------------------- split operands
+#
+# The kernels that split each float32 operand into three bfloat16 terms, against
+# 64 bits: inputs whose contractions can be read out of one call without a tanh
+# that matters, in shapes that take 32-window tiles (d 64, window 5, H 32, from
+# 3,585 windows on: one and eight tiles per workgroup) and the wide path (16, 32
+# and 64 windows per forward workgroup).
+SPLIT_SHAPES = [(64, 5, 32, 4096), (64, 5, 32, 65_536), (128, 3, 128, 64), (192, 3, 192, 8192),
+                (256, 3, 256, 16_384)]
+
+
+def split_operands(kind, n, m):
+    """x[n][m], y[n] of a contraction out[j] = sum_i x[i][j] y[i]."""
+    rng = np.random.default_rng(zlib.crc32(kind.encode()))
+    if kind.startswith("0x"):  # equal entries: what a product loses adds up with one sign
+        v = np.array([int(kind, 16)], np.uint32).view(np.float32)[0]
+        return np.full((n, m), v, np.float32), np.full(n, v, np.float32)
+    x = rng.standard_normal((n, m)).astype(np.float32)
+    y = rng.standard_normal(n).astype(np.float32)
+    if kind == "cancel":  # the second half takes the first away, up to 2^-12 of it
+        h = n // 2
+        x[h:] = -x[:h] * np.float32(1 + 2.0**-12)
+        y[h:] = y[:h]
+    return x, y
+
+
+def split_contraction(which, kind, shape):
+    """One training step whose updated parameters show one contraction: (what the
+    GPU gives, the same in 64 bits, sum |x y|, terms).  B is a power of two, so
+    1 / B is exact; Z is a row of zeros, and lr is 1."""
+    d, win, H, B = shape
+    V, Z, mid = 300, 299, win // 2
+    p = {"E": np.zeros((V, d), np.float32), "W1": np.zeros((H, win * d), np.float32),
+         "b1": np.zeros(H, np.float32), "w2": np.zeros(H, np.float32),
+         "b2": np.zeros(1, np.float32)}
+    ids, cor = np.full((B, win), Z, np.int32), np.full(B, Z, np.int32)
+    cols = slice(mid * d, (mid + 1) * d)
+    small = np.float32(2.0**-20)
+    if which == "G":  # E = 0: the centre's dz is -w2 / B
+        x, y = split_operands(kind, H, d)
+        p["W1"][:, cols], p["w2"] = x, y
+        ids[0, mid] = 0
+        n = H
+    elif which == "dW1":  # W1 = 0: the same; the first n windows have a row that is not 0
+        n = 32 if kind.startswith("0x") else min(B, 256)
+        x, w = split_operands(kind, n, d)
+        p["E"][:n], p["w2"][:] = x, np.resize(w, H)
+        ids[:n, mid] = np.arange(n)
+    elif which == "centre":  # w2 = 0: its gradient is tanh(z - z~) / B of window 0
+        x, y = split_operands(kind, d, H)
+        p["W1"][:, cols], p["E"][0] = x.T * small, y
+        ids[0, mid] = 0
+        n = d
+    else:  # "context": z - z~ = 2^-20, and db1 = 2^-20 (z + z~) / B of window 0
+        x, y = split_operands(kind, d, H)
+        p["W1"][:, :d], p["E"][0] = x.T * small, y
+        p["W1"][:, mid * d], p["E"][1, 0] = small, 1
+        p["w2"][:] = 1
+        ids[0, 0], ids[0, mid] = 0, 1
+        n = d
+    pd = params_dev(p)
+    ctx = pg().Context(V, d, win, H, max_batch=B)
+    ctx.train_step(pd, dev(ids), dev(cor), 1.0)
+    assert ctx.status() == pg().OK
+    got = {k: host(v).astype(np.float64) * B for k, v in pd.items()}
+    x64, y64 = x.astype(np.float64), p["w2"].astype(np.float64)
+    if which == "dW1":
+        return (got["W1"][:, cols], y64[:, None] * x64.sum(0), np.abs(y64)[:, None] * np.abs(x64).sum(0), n)
+    ref, size = y.astype(np.float64) @ x64, np.abs(y).astype(np.float64) @ np.abs(x64)
+    if which == "G":
+        return got["E"][0], ref, size, n
+    if which == "centre":
+        return got["w2"] * 2.0**20, np.tanh(ref * 2.0**-20) * 2.0**20, size, n
+    zc = ref * 2.0**-20
+    out = -np.tanh(2.0**-20) * (np.tanh(zc + 2.0**-20) + np.tanh(zc)) / 2
+    return got["b1"] / 2 * 2.0**40, out * 2.0**40, size, n
+
+
+@pytest.mark.parametrize("kind", ["0x3f80ff80", "0x3f807fc0", "cancel", "random"])
+@pytest.mark.parametrize("which", ["G", "dW1", "centre", "context"])
+@pytest.mark.parametrize("shape", SPLIT_SHAPES, ids=["x".join(map(str, s)) for s in SPLIT_SHAPES])
+def test_split_contractions_against_64_bits(shape, which, kind):
+    """A product loses at most 2^-24 of itself (terms rounded to nearest: the
+    second is within 2^-8 of the operand's leading bit, the third within 2^-17);
+    the first products and the rest are added up apart, and then the sum and the
+    updated parameter round once each: 3 x 2^-24 of sum |x y|, and one rounding
+    more for each 32-term step where the sum of the first products is not exact.
+    (Equal entries' is: 16 bits each, at most 256 of them.)  The context's
+    result passes three more operations.  0x3f80ff80 is the number whose square
+    a truncated first term loses most of (2^-22.02), 0x3f807fc0 the one that
+    rounded terms do (2^-24.01); a lost third term would be 2^-17."""
+    got, ref, size, n = split_contraction(which, kind, shape)
+    bar = (3 + (0 if kind.startswith("0x") else n // 32) + (3 if which == "context" else 0)) * 2.0**-24
+    err = np.abs(got - ref) / size
+    print(f"{which} {kind} {shape}: {err.max() / 2.0**-24:.2f} of {bar / 2.0**-24:.0f} x 2^-24, "
+          f"norm {np.linalg.norm(got - ref) / np.linalg.norm(ref):.2e}")
+    assert np.all(err <= bar), float(err.max() / 2.0**-24)
+
+
+@pytest.mark.parametrize("name", ["E", "W1"])
+@pytest.mark.parametrize("shape", SPLIT_SHAPES[::2], ids=["x".join(map(str, s)) for s in SPLIT_SHAPES[::2]])
+def test_split_nan_payloads(shape, name):
+    """A NaN with its payload in the lower 16 bits (0x7f800001) has the effect of
+    the default one: nothing of it is an infinity."""
+    d, win, H, B = shape
+    w = workloads.Workload("nan", V=300, d=d, win=win, H=H, B=B, lr=0.05, steps=1, zipf_s=1.0,
+                           seed=26)
+    ids, cor = workloads.batch(w, 0, B)
+    outs = []
+    for bits in (0x7fc00000, 0x7f800001):
+        p = workloads.init_params(w)
+        p[name].view(np.uint32)[3, 5] = bits
+        pd = params_dev(p)
+        ctx = pg().Context(w.V, d, win, H, max_batch=B)
+        loss = torch.zeros(1, device="cuda")
+        scores = host(ctx.score(pd, dev(ids)))
+        ctx.train_step(pd, dev(ids), dev(cor), w.lr, loss)
+        outs.append([scores, host(loss)] + [host(pd[k]) for k in sorted(pd)])
+    assert np.isnan(outs[0][0]).any()
+    for a, b in zip(*outs):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("value", [3.4e38, -3.4e38])
+@pytest.mark.parametrize("shape", [(64, 5, 32, 4096), (64, 3, 128, 20)], ids=["tiles", "wide"])
+def test_split_values_above_the_largest_bfloat16(shape, value):
+    """A finite value that would round to an infinite first term (one element
+    of one window's row, times +-2^-126: pre-activations of +-4)."""
+    d, win, H, B = shape
+    w = workloads.Workload("big", V=300, d=d, win=win, H=H, B=B, lr=0.05, steps=1, zipf_s=1.0,
+                           seed=27)
+    p = workloads.init_params(w)
+    ids, cor = workloads.batch(w, 0, B)
+    ids, cor = np.minimum(ids, 298), np.minimum(cor, 298)
+    ids[0, 0] = 299
+    p["E"][299, 5] = value
+    p["W1"][:, 5] = np.copysign(np.float32(2.0**-126), p["W1"][:, 5])
+    pd = params_dev(p)
+    ctx = pg().Context(w.V, d, win, H, max_batch=B)
+    loss = torch.zeros(1, device="cuda")
+    scores = host(ctx.score(pd, dev(ids)))
+    ctx.train_step(pd, dev(ids), dev(cor), w.lr, loss)
+    np.testing.assert_allclose(scores, oracle.score(p, ids), rtol=1e-5, atol=1e-6)
+    np.testing.assert_allclose(host(loss)[0], oracle.train_step(p, ids, cor, w.lr), rtol=1e-5)
+    for k in p:
+        assert np.isfinite(host(pd[k])).all(), k
+    for k in ("b1", "w2"):
+        np.testing.assert_allclose(host(pd[k]), p[k], rtol=1e-4, atol=1e-4 * rms(p[k]))
+
+
 @pytest.mark.parametrize("w", LARGE_SHAPES[:2], ids=[w.name for w in LARGE_SHAPES[:2]])
 def test_large_hidden_layer_scores(w):
     p = workloads.init_params(w)
