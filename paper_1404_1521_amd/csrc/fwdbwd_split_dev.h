@@ -19,20 +19,23 @@
 //   F  forward: partial sums over the column steps (the centre block's true
 //      and corrupted sums apart: z = zc + zctr, z~ = zc + zcor, §1 model, x~)
 //   E  epilogue: wave (row tile w & 1, row w >> 1 of each group of four)
-//   B  dW1 (accumulated across tiles in registers) and G; the next tile's
-//      rows, in flight since F, are split by one wave of each SIMD before and
-//      by the other after its matrix instructions
+//   B  dW1 (a tile's first products and the rest apart, as everywhere; their
+//      sum joins the registers' total of the tiles) and G; the next tile's
+//      rows, in flight since F, are split after the matrix instructions
 //   S  the split rows go to LDS
-// Timestamps at B = 65,536 (8 tiles per workgroup, cycles at about 2.1 GHz): W1
+// Timestamps at B = 65,536 (8 tiles per workgroup, cycles at about 2.1 GHz; before
+// the terms were rounded to nearest and a tile's sums kept apart, which cost 2.3
+// of 53.8 us per launch): W1
 // and the first rows 10,400, then per tile F 4,300, E 2,200, B 5,500, S 1,100.
 // The 108 matrix instructions of a wave take 3,460 of them on a SIMD of two
 // waves (counters: 19% of a launch): the rest is vector-ALU work (splits, tanh, sums, addresses) that the
 // barriers keep from running under them.  Against the float32 form it replaced
 // (12 waves in roles, 42% of the cycles in matrix instructions at 4 times the
-// number): 71 -> 55 us per launch at B = 65,536, 29 -> 20 us at 16,384.  The
+// number): 71 -> 56 us per launch at B = 65,536, 29 -> 22 us at 16,384.  The
 // gradients' error against 64 bits (norm of the difference over the norm, six
-// batches of 65,536 and of 4,096): rows of E 6.1e-8 in both forms, W1 6.4e-8 ->
-// 6.1e-8, b1 1.8e-7 -> 1.1e-7, w2 1.1e-7 -> 7e-8.
+// batches of 65,536): rows of E 5.6e-8 -> 5.5e-8, W1 6.5e-8 -> 5.7e-8, b1 1.9e-7
+// -> 1.0e-7, w2 1.2e-7 -> 6.9e-8; of 4,096: 5.8e-8 -> 5.2e-8, 6.4e-8 -> 5.5e-8,
+// 1.7e-7 -> 1.2e-7, 9.7e-8 -> 7.6e-8.
 #pragma once
 #include "common.h"
 #include "large_dev.h"
@@ -338,12 +341,18 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
 #pragma unroll
         for (int p = 0; p < 3; ++p)
           Bv[p] = fs_read_tr(x0 + 2 * p * kWave, x0 + 2 * (3 + p) * kWave);
+        f4 hi[2] = {kZero4, kZero4}, lo[2] = {kZero4, kZero4};
 #pragma unroll
         for (int p = 0; p < 5; ++p)
 #pragma unroll
-          for (int n = 0; n < 2; ++n) accW[u][n] = lg_mfma(A[n][PA[p]], Bv[PB[p]], accW[u][n]);
+          for (int n = 0; n < 2; ++n) lo[n] = lg_mfma(A[n][PA[p]], Bv[PB[p]], lo[n]);
 #pragma unroll
-        for (int n = 0; n < 2; ++n) accW[u][n] = lg_mfma(A[n][0], Bv[0], accW[u][n]);
+        for (int n = 0; n < 2; ++n) hi[n] = lg_mfma(A[n][0], Bv[0], hi[n]);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) accW[u][n] += lg_sum(hi[n], lo[n]);
+        // (keeps the sums out of the compiler's reach: it spills 24 to 69 registers
+        // over the loop without this)
+        asm volatile("" : "+v"(accW[u][0]), "+v"(accW[u][1]));
       }
       lg_pin();
       // G: V (row tiles m) times W1's 16 columns

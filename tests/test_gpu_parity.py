@@ -828,6 +828,27 @@ def test_split_values_above_the_largest_bfloat16(shape, value):
         np.testing.assert_allclose(host(pd[k]), p[k], rtol=1e-4, atol=1e-4 * rms(p[k]))
 
 
+def test_split_infinite_gradient():
+    """An infinite output weight on windows with h < 0 < h~ makes its row of
+    dW1 an infinity of one sign, as a float32 chain gives it, not a NaN; the
+    other hidden units stay finite."""
+    d, win, H, B = SPLIT_SHAPES[0]
+    p = {"E": np.zeros((10, d), np.float32), "W1": np.full((H, win * d), 0.01, np.float32),
+         "b1": np.zeros(H, np.float32), "w2": np.full(H, 0.1, np.float32),
+         "b2": np.zeros(1, np.float32)}
+    p["E"][0], p["E"][1], p["E"][2] = -0.5, 0.25, 0.02
+    p["w2"][3] = np.inf
+    ids, cor = np.full((B, win), 2, np.int32), np.ones(B, np.int32)
+    ids[:, win // 2] = 0
+    pd = params_dev(p)
+    ctx = pg().Context(10, d, win, H, max_batch=B)
+    ctx.train_step(pd, dev(ids), dev(cor), 0.5)
+    assert ctx.status() == pg().OK
+    W1 = host(pd["W1"])
+    assert np.all(W1[3] == -np.inf), W1[3]
+    assert np.isfinite(np.delete(W1, 3, 0)).all()
+
+
 @pytest.mark.parametrize("w", LARGE_SHAPES[:2], ids=[w.name for w in LARGE_SHAPES[:2]])
 def test_large_hidden_layer_scores(w):
     p = workloads.init_params(w)
