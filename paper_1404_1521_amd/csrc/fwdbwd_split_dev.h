@@ -99,7 +99,7 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
     if (t < R * W1P && b < a.B) id = j < Sh::WIN ? a.windows[(size_t)b * Sh::WIN + j] : a.corrupt[b];
     return id;
   };
-  auto store_id = [&](int buf, int32_t id) LG_INLINE {  // rows >= B and bad ids read row 0
+  auto store_id = [&](int buf, int32_t id) LG_INLINE {  // (rows >= B and bad ids read row 0)
     const bool bad = (uint32_t)id >= (uint32_t)a.V;
     if (bad) atomicOr(a.flag, kFlagBadId);
     if (t < R * W1P) idt[buf * R * W1P + t] = bad ? 0 : id;
@@ -118,8 +118,14 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
     }
   };
   lu4 xp[3][3];
-  auto split_x = [&]() LG_INLINE {
+  auto split_x = [&](int tile) LG_INLINE {
     float x[3][8], big = 0.f;
+    if ((tile + 1) * R > a.B)  // rows past the batch are zero (a NaN of row 0 would reach dW1)
+#pragma unroll
+      for (int v = 0; v < 3; ++v) {
+        const int u = t + v * NT;
+        if (tile * R + 16 * ((u >> 6) & 1) + (u & 15) >= a.B) xr[v][0] = xr[v][1] = kZero4;
+      }
 #pragma unroll
     for (int v = 0; v < 3; ++v) {
 #pragma unroll
@@ -199,7 +205,7 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
     w2v[n] = h < a.H ? a.w2[h] : 0.f;
   }
   const float b2v = a.b2[0];
-  split_x();
+  split_x(tile0);
   store_x();
   store_id(1, idn);
   __syncthreads();
@@ -282,19 +288,20 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
       ps = fs_row_sum(ps);
       pst = fs_row_sum(pst);
       const float mg = 1.f - (b2v + ps) + (b2v + pst);
-      const bool on = row < a.B && mg > 0.f;  // hinge active (derivative 0 at margin 0)
+      const bool live = row < a.B;           // rows past the batch add nothing, whatever they hold
+      const bool on = live && mg > 0.f;       // hinge active (derivative 0 at margin 0)
       const float gst = on ? a.invB : 0.f;    // d loss/d s~ = m/B, d loss/d s = -m/B
       uint16_t* vt = reinterpret_cast<uint16_t*>(vs) + (m * kWave + lane) * 4 + q;
       float v[2][3], big = 0.f;
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
         const float gw = gst * w2v[n];
-        v[n][0] = gw * hmh[n] * (h[n] + ht[n]);
-        v[n][1] = -gw * (1.f - h[n] * h[n]);
-        v[n][2] = gw * (1.f - ht[n] * ht[n]);
+        v[n][0] = live ? gw * hmh[n] * (h[n] + ht[n]) : 0.f;
+        v[n][1] = live ? -gw * (1.f - h[n] * h[n]) : 0.f;
+        v[n][2] = live ? gw * (1.f - ht[n] * ht[n]) : 0.f;
         lg_largest(v[n], big);
         db1a[n] += v[n][0];
-        dw2a[n] -= gst * hmh[n];  // -(m/B) h + (m/B) h~
+        dw2a[n] -= live ? gst * hmh[n] : 0.f;  // -(m/B) h + (m/B) h~
       }
       lg_checked(big, [&](auto safe) LG_INLINE {
 #pragma unroll
@@ -385,7 +392,7 @@ __device__ inline void fwdbwd_split(const FwdArgs& a, int wg, char* lds) {
         }
       }
     }
-    if (more) split_x();
+    if (more) split_x(tile0 + tt + 1);
     __syncthreads();
 
     // ---- S

@@ -468,9 +468,9 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
           vr[0] = dsum;
           vr[a.H] = dz;
           vr[2 * a.H] = dzt;
+          db1[n] += dsum;
+          dw2[n] -= gst * hmh;  // -(m/B) h + (m/B) h~
         }
-        db1[n] += dsum;
-        dw2[n] -= gst * hmh;  // -(m/B) h + (m/B) h~
       }
     }
   float* vp = a.vpart + (size_t)blockIdx.x * (2 * a.H + 2);

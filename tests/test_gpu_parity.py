@@ -849,6 +849,28 @@ def test_split_infinite_gradient():
     assert np.isfinite(np.delete(W1, 3, 0)).all()
 
 
+# Batches that leave part of their last tile empty: 16 of a 32-window tile's
+# windows, 32 of a 64-window forward workgroup's, 9 of 16.
+@pytest.mark.parametrize("d,win,H,B", [(64, 5, 32, 3600), (128, 3, 128, 8224), (64, 3, 128, 23)])
+def test_padding_windows_take_nothing_from_row_0(d, win, H, B):
+    w = workloads.Workload("pad", V=300, d=d, win=win, H=H, B=B, lr=0.05, steps=1, zipf_s=1.0,
+                           seed=28)
+    ids, cor = workloads.batch(w, 0, B)
+    ids, cor = np.maximum(ids, 1), np.maximum(cor, 1)
+    outs = []
+    for fill in (0.0, np.nan):
+        p = workloads.init_params(w)
+        p["E"][0] = fill
+        pd = params_dev(p)
+        loss = torch.zeros(1, device="cuda")
+        ctx = pg().Context(w.V, d, win, H, max_batch=B)
+        ctx.train_step(pd, dev(ids), dev(cor), w.lr, loss)
+        outs.append([host(loss), host(pd["E"])[1:]] + [host(pd[k]) for k in ("W1", "b1", "w2", "b2")])
+    for a, b in zip(*outs):
+        assert np.isfinite(a).all()
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("w", LARGE_SHAPES[:2], ids=[w.name for w in LARGE_SHAPES[:2]])
 def test_large_hidden_layer_scores(w):
     p = workloads.init_params(w)
