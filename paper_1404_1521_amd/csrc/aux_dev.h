@@ -89,16 +89,29 @@ __global__ __launch_bounds__(kBlock) void k_score(ScoreArgs a) {
 //
 // A wave copies a.rows consecutive entries (rows of X and Xc): each lane looks
 // up one entry, and the rows then go as one flat list of 16-byte words,
-// kGatherU of them in flight per lane.  An entry's position is divided out
-// once per row and not once per word, and by 32-bit arithmetic.  The stores are
-// non-temporal: X is written once and several times the size of the rows read,
-// which would lose their place in the caches to it.  16,384 windows of 11
-// rows of 128 out of a 512 MB table (140 MB in and out), three outputs in
-// turn: 37.7 us with a thread per word and two 64-bit divisions, 33.5 us this
-// way with plain stores, 24.2 us (5.8 TB/s) with these; 65,536 windows of 5
-// rows of 64: 34.6, 31.7 and 22.0 us.
-constexpr int kGatherU = 8;
+// U of them in flight per lane.  An entry's position is divided out once per row
+// and not once per word, and by 32-bit arithmetic.
+//
+// NT: non-temporal stores, for outputs that the L2s cannot hold (kGatherKeep):
+// X is written once and several times the size of the rows read, which would
+// lose their place in the caches to it.  Smaller outputs are left there for
+// whoever reads X next, and two words per lane in flight fill the chip as well
+// as eight.  us per call alone | followed by an addition over X | by a product of
+// X with 64 columns, calls in a graph, non-temporal and eight words against plain
+// and two (outputs; rows of 64 or 128):
+//     0.8 MB   3.0, 2.6 |  5.1,  4.4 | 11.4,  9.0
+//     6.3 MB   3.7, 3.5 |  8.1,  7.6 | 13.7, 11.4
+//    12.6 MB   4.3, 4.7 | 11.8, 11.7 | 16.4, 14.3
+//    25.2 MB   6.6, 7.2 | 18.1, 16.6 | 23.6, 19.1 (rows of 64)
+//    25.2 MB   6.6, 7.3 | 19.6, 16.7 | 27.5, 21.9 (rows of 128)
+//    50.3 MB  11.2, 13.2 | 28.8, 26.8 | 30.6, 29.7
+//   100.7 MB  24.4, 25.4 | 53.9, 55.8 | 53.1, 52.4
+// 65,536 windows of 5 rows of 64 (100.7 MB), three outputs in turn: a thread per
+// word with two 64-bit divisions 34.6 us, eight words with plain stores 31.7,
+// non-temporal 22.0.
+constexpr size_t kGatherKeep = (size_t)32 << 20;  // bytes: the eight L2s of 4 MB
 
+template <int U, bool NT>
 __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a) {
   __shared__ int2 ent[kWavesPerBlock][kWave];  // (id or -1, row of X or ~row of Xc)
   const int t = threadIdx.x, lane = t & (kWave - 1);
@@ -119,11 +132,11 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a) {
   }
   wave_lds_sync();
   const int total = nr * q4;
-  for (int f0 = lane; f0 < total; f0 += kWave * kGatherU) {
-    f4 v[kGatherU];
-    float* dst[kGatherU];
+  for (int f0 = lane; f0 < total; f0 += kWave * U) {
+    f4 v[U];
+    float* dst[U];
 #pragma unroll
-    for (int u = 0; u < kGatherU; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int f = min(f0 + u * kWave, total - 1);
       const int r = (int)((uint32_t)f * a.rq4 >> 20), q = f - r * q4;  // f / q4: f < 4096
       const int2 x = ent[w][r];
@@ -133,8 +146,11 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a) {
       if (x.x >= 0) v[u] = ld4(a.E + (size_t)x.x * a.d + 4 * q);
     }
 #pragma unroll
-    for (int u = 0; u < kGatherU; ++u)
-      if (f0 + u * kWave < total) __builtin_nontemporal_store(v[u], reinterpret_cast<f4*>(dst[u]));
+    for (int u = 0; u < U; ++u)
+      if (f0 + u * kWave < total) {
+        if constexpr (NT) __builtin_nontemporal_store(v[u], reinterpret_cast<f4*>(dst[u]));
+        else st4(dst[u], v[u]);
+      }
   }
 }
 

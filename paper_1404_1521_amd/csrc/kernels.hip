@@ -447,7 +447,9 @@ hipError_t launch_gather(const GatherArgs& a, const Launch& L) {
   g.rows = kWave;
   while (g.rows > 4 && N / g.rows < 8 * kCus) g.rows /= 2;
   g.rq4 = ((1u << 20) + q4 - 1) / q4;
-  return pg_launch(k_gather, dim3(ceil_div(N, g.rows * kWavesPerBlock)), dim3(kBlock), 0, L, g);
+  const dim3 grid(ceil_div(N, g.rows * kWavesPerBlock));
+  if ((size_t)N * a.d * 4 > kGatherKeep) return pg_launch(k_gather<8, true>, grid, dim3(kBlock), 0, L, g);
+  return pg_launch(k_gather<2, false>, grid, dim3(kBlock), 0, L, g);
 }
 
 }  // namespace pg

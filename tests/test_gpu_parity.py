@@ -150,9 +150,11 @@ def scatter_bound(t0, idx, Y, alpha):
 
 
 # Row widths that do and do not divide a wave, one entry to many per wave, a
-# last wave with fewer rows than the others, and out-of-range ids.
+# last wave with fewer rows than the others, both sides of the switch to
+# non-temporal stores (32 MB: 5,461 windows of 12 rows of 128), and out-of-range
+# ids.
 @pytest.mark.parametrize("d,win,B", [(112, 3, 97), (256, 1, 3), (16, 31, 1001), (192, 5, 6000),
-                                     (64, 7, 20_003)])
+                                     (64, 7, 20_003), (128, 11, 5461), (128, 11, 5462)])
 def test_gather_row_widths(d, win, B):
     rng = np.random.default_rng([d, win, B])
     E = rng.standard_normal((3000, d), dtype=np.float32)
