@@ -511,8 +511,8 @@ __global__ __launch_bounds__(NW * kWave) void k_large_fwd(LargeArgs a) {
 template <int HW, int CW>
 __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
   constexpr int H = 64 * HW, CB = 64 * CW, NT = HW * CW * kWave;
-  constexpr int VU = H * 4 / NT;                  // V units (a column of 8 windows) per thread
-  constexpr int XU = (CB * 4 + NT - 1) / NT;      // X units per thread
+  constexpr int VU = 4 / CW;                      // V units (a column of 8 windows) per thread
+  constexpr int XU = (4 + HW - 1) / HW;           // X units per thread
   constexpr int VF = (H / 16) * 3 * kWave, XF = (CB / 16) * 3 * kWave;
   extern __shared__ lu4 lds_q[];
   lu4* Vs = lds_q;                                // [2][VF]
@@ -539,27 +539,31 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
   __syncthreads();
 
   const float* vbase = a.V + (size_t)b_lo * 3 * H + (size_t)ty * H;
+  // this thread's units: column vh of V, groups of eight windows vg, vg + CW, ..
+  // and column xc of X, groups xg, xg + HW, .. (NT is CW H and HW CB; a wave's
+  // groups are the same for its lanes)
+  const int vh = t % H, vg = w / HW, xc = t % CB, xg = w / CW;
   float vr[VU][8], xr[XU][8];
   auto load_t = [&](auto tail, int st) LG_INLINE {  // tail: the step has windows past the slice
     constexpr bool TAIL = decltype(tail)::value;
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
-      const int x = t + u * NT, r = 32 * st + 8 * (x / H);
+      const int r = 32 * st + 8 * (vg + CW * u);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int re = TAIL ? min(r + e, nb - 1) : r + e;
-        vr[u][e] = vbase[re * 3 * H + x % H];
+        vr[u][e] = vbase[re * 3 * H + vh];
         if (TAIL && r + e >= nb) vr[u][e] = 0.f;
       }
     }
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
-      const int x = t + u * NT, r = 32 * st + 8 * (x / CB);
-      if (CB * 4 % NT == 0 || x < CB * 4) {
+      const int r = 32 * st + 8 * (xg + HW * u);
+      if (4 % HW == 0 || xg + HW * u < 4) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int re = TAIL ? min(r + e, nb - 1) : r + e;
-          xr[u][e] = a.E[(size_t)ids[re] * d + off0 + x % CB];
+          xr[u][e] = a.E[(size_t)ids[re] * d + off0 + xc];
         }
       }
     }
@@ -574,26 +578,24 @@ __global__ __launch_bounds__(HW * CW * kWave) void k_large_dw1(LargeArgs a) {
     for (int u = 0; u < VU; ++u) lg_largest(vr[u], big);
 #pragma unroll
     for (int u = 0; u < XU; ++u)
-      if (CB * 4 % NT == 0 || t + u * NT < CB * 4) lg_largest(xr[u], big);
+      if (4 % HW == 0 || xg + HW * u < 4) lg_largest(xr[u], big);
     lg_checked(big, [&](auto safe) LG_INLINE {
       constexpr bool SAFE = decltype(safe)::value;
       lu4 p[3];
 #pragma unroll
       for (int u = 0; u < VU; ++u) {
-        const int x = t + u * NT, h = x % H, gq = x / H;
         lg_split8<SAFE>(vr[u], p);
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-          Vs[buf * VF + ((h >> 4) * 3 + k) * kWave + 16 * gq + (h & 15)] = p[k];
+          Vs[buf * VF + ((vh >> 4) * 3 + k) * kWave + 16 * (vg + CW * u) + (vh & 15)] = p[k];
       }
 #pragma unroll
       for (int u = 0; u < XU; ++u) {
-        const int x = t + u * NT, col = x % CB, gq = x / CB;
-        if (CB * 4 % NT == 0 || x < CB * 4) {
+        if (4 % HW == 0 || xg + HW * u < 4) {
           lg_split8<SAFE>(xr[u], p);
 #pragma unroll
           for (int k = 0; k < 3; ++k)
-            Xs[buf * XF + ((col >> 4) * 3 + k) * kWave + 16 * gq + (col & 15)] = p[k];
+            Xs[buf * XF + ((xc >> 4) * 3 + k) * kWave + 16 * (xg + HW * u) + (xc & 15)] = p[k];
         }
       }
     });
