@@ -359,14 +359,22 @@ __device__ void fwdbwd8_wg(const FwdArgs& a, int wg, float* lds) {
     // and the end of the pair's dW1 before the next pair's rows overwrite
     // the single X buffer).  tiles_per_wg is even, so the second tile of a
     // pair is this workgroup's, or past the last tile (rows >= B).
+    // The next pair's ids take one set of registers: their rows are addressed
+    // before the ids of the pair after it replace them.  (ids[(gi + 1) & 1] and
+    // ids[gi & 1], indexed by the loop's counter, came out of the compiler with one
+    // condition for both writes: an odd gi wrote neither, and every second pair from
+    // the fourth on read row 0.)
     const int ng = (ntl + 1) / 2;
+    int32_t idn[XPT];
+#pragma unroll
+    for (int p = 0; p < XPT; ++p) idn[p] = ids[1][p];
     for (int gi = 0; gi < ng; ++gi) {
       const int row0 = (tile0 + 2 * gi) * kTileRows;
       store_x(0, xr);
       __syncthreads();  // X of this pair (and W1) staged
       if (gi + 1 < ng) {
-        load_x(ids[(gi + 1) & 1], xr);                                // rows of the next pair
-        if (gi + 2 < ng) load_ids(tile0 + 2 * (gi + 2), ids[gi & 1]);  // ids two pairs ahead
+        load_x(idn, xr);                                         // rows of the next pair
+        if (gi + 2 < ng) load_ids(tile0 + 2 * (gi + 2), idn);    // ids two pairs ahead
       }
       forward(xl);
       __syncthreads();  // forward partials written

@@ -586,6 +586,23 @@ def test_role_specialised_tiles_ragged(B):
     run_both(w, 2, B, 0)
 
 
+@pytest.mark.parametrize("B,pairs,last,windows", [(4100, 1, 1, 4), (8215, 2, 2, 7), (8231, 2, 3, 7),
+                                                   (12_289, 2, 1, 1), (16_384, 2, 4, 16),
+                                                   (20_011, 3, 3, 11), (32_773, 5, 9, 5)])
+def test_tile_pairs_ragged(B, pairs, last, windows):
+    """The d 16 shape's pairs of 16-window tiles (above 4,096 windows): up to
+    `pairs` pairs per workgroup, `last` tiles in the last one (an odd number
+    leaves half a pair), `windows` windows in the last tile."""
+    ntiles = -(-B // 16)
+    per = -(-ntiles // 256)
+    per += per & 1
+    assert per == 2 * pairs and last == (ntiles - 1) % per + 1
+    assert windows == B - 16 * (ntiles - 1)
+    w = workloads.Workload("w5_d16_h8", V=20_000, d=16, win=5, H=8, B=B, lr=0.5, steps=2,
+                           zipf_s=1.0, seed=32)
+    run_both(w, 2, B, 0)
+
+
 # Both sides of the switch to 32-window tiles (3,585 windows), hidden layers that
 # leave padding rows, a last tile of one window, the atomic update; and the d 16
 # shape's tile pairs, the last workgroup with one tile.
