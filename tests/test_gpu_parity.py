@@ -559,29 +559,14 @@ def test_update_forms_at_their_limits(B):
     run_both(w, 2, B, 0)
 
 
-@pytest.mark.parametrize("B", [4100, 8215, 8231])
-def test_pipelined_tiles_ragged(B):
-    """Batches of the 32-window tiles: 129 tiles at one per workgroup, 257 and
-    258 at two (the last workgroup has one or both); the last tile holds 4, 23
-    or 7 windows.  (Cut into 16-window tiles, as the asserts count them, they
-    fill no even share per workgroup either.)"""
-    ntiles = -(-B // 16)
-    per = -(-ntiles // 256)
-    per += per & 1
-    assert per > 1 and ntiles % per != 0
-    w = PRESETS["sweep_1024"].with_batch(B)
-    run_both(w, 2, B, 0)
-
-
-@pytest.mark.parametrize("B", [32653, 32773])
-def test_role_specialised_tiles_ragged(B):
-    """Large batches of the 32-window tiles: 1021 tiles at four per workgroup
-    leave the last workgroup one tile, 1025 at five leave it all; the last
-    tile holds 13 or 5 windows."""
-    ntiles = -(-B // 16)
-    per = -(-ntiles // 256)
-    per += per & 1
-    assert per >= 8 and ntiles % per in (1, 9) and B % 16 != 0
+@pytest.mark.parametrize("B,per,last,windows", [(4100, 1, 1, 4), (8215, 2, 1, 23), (8231, 2, 2, 7),
+                                                 (32_653, 4, 1, 13), (32_773, 5, 5, 5)])
+def test_split_tiles_ragged(B, per, last, windows):
+    """Batches that fill no even share of 32-window tiles: `per` tiles per
+    workgroup, `last` in the last one, `windows` windows in the last tile."""
+    ntiles = -(-B // 32)
+    assert per == -(-ntiles // 256) and last == (ntiles - 1) % per + 1
+    assert windows == B - 32 * (ntiles - 1)
     w = PRESETS["sweep_1024"].with_batch(B)
     run_both(w, 2, B, 0)
 
@@ -604,10 +589,11 @@ def test_tile_pairs_ragged(B, pairs, last, windows):
 
 
 # Both sides of the switch to 32-window tiles (3,585 windows), hidden layers that
-# leave padding rows, a last tile of one window, the atomic update; and the d 16
-# shape's tile pairs, the last workgroup with one tile.
+# leave padding rows, a last tile of one window, the atomic update; and of the
+# switch of the d 16 shape to tile pairs (4,097 windows).
 @pytest.mark.parametrize("d,H,B,mode", [(64, 32, 3584, 0), (64, 32, 3585, 0), (64, 17, 3585, 1),
-                                        (64, 25, 8193, 0), (64, 31, 16_417, 0), (16, 8, 4100, 0)])
+                                        (64, 25, 8193, 0), (64, 31, 16_417, 0), (16, 8, 4096, 0),
+                                        (16, 16, 4097, 1)])
 def test_split_tiles_at_their_limits(d, H, B, mode):
     w = workloads.Workload(f"w5_d{d}_h{H}", V=20_000, d=d, win=5, H=H, B=B, lr=0.5, steps=2,
                            zipf_s=1.0, seed=31)
@@ -667,12 +653,17 @@ def test_large_hidden_layer_shapes(w, mode):
     run_both(w, w.steps, w.B, mode)
 
 
-# The wide path's other forms: 32 and 64 windows per forward workgroup (from
-# 4,097 and 8,193 windows), every column grouping of the rows G (d 64 .. 256),
-# one and two workgroups per position range, window 1 (no context positions),
+# The wide path's other forms, beyond the 16 windows per forward workgroup and the
+# few positions of the shapes above: every (hidden units, windows per workgroup)
+# of the forward and the scores (H 128, 192, 256 x 32 from 4,097 windows; 64 from
+# 8,193, but for H 192), every column grouping of the rows G (d 64 .. 256), context
+# positions taken whole by a group of waves, left over and split by windows, in
+# one and in several workgroups per 64 windows, window 1 (no context positions),
 # batches one past a 16-, 32- or 64-window tile.
 @pytest.mark.parametrize("d,win,H,B", [(128, 3, 128, 4097), (64, 3, 192, 8193), (256, 1, 128, 33),
-                                       (128, 1, 256, 65), (192, 3, 256, 17)])
+                                       (128, 1, 256, 65), (192, 3, 256, 17), (64, 7, 128, 8193),
+                                       (128, 5, 256, 4097), (128, 3, 256, 8193), (64, 11, 128, 16_385),
+                                       (128, 7, 128, 16_385)])
 def test_wide_forms(d, win, H, B):
     w = workloads.Workload(f"w{win}_d{d}_h{H}", V=2500, d=d, win=win, H=H, B=B, lr=0.05, steps=1,
                            zipf_s=1.0, seed=24)
