@@ -380,7 +380,7 @@ int enqueue_compute(polyglot_ctx* ctx, float* E, float* W1, float* b1, float* w2
     fa.tiles_per_wg = ceil_div(fa.ntiles, shape8 ? std::min(ctx->max_parts, kF8MaxWorkgroups)
                                                  : ctx->max_parts);
     // the pair form takes an even number of tiles per workgroup
-    if (shape8 && kF8MultiForm == 2 && fa.tiles_per_wg > 1) fa.tiles_per_wg += fa.tiles_per_wg & 1;
+    if (shape8 && fa.tiles_per_wg > 1) fa.tiles_per_wg += fa.tiles_per_wg & 1;
     n_fb = ceil_div(fa.ntiles, fa.tiles_per_wg);
     // one tile per workgroup and CUs to spare: two workgroups per tile, each
     // taking half of its backward (the forward runs in both).  Only the

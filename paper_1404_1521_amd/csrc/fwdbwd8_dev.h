@@ -7,9 +7,9 @@
 //   X         the tile's embedding rows -- positions 0..win-1 and the
 //             corrupt row as position win -- staged in LDS once, laid out
 //             [position][column quad][window] so that both MFMA operand
-//             layouts read it without bank conflicts; the rows of tile k+1
-//             are loaded into registers while tile k computes, and the ids
-//             of tile k+2 are loaded at the same time;
+//             layouts read it without bank conflicts; the rows of the next
+//             pair are loaded into registers while a pair computes, and the
+//             ids of the pair after it at the same time;
 //   forward   Z = X W1^T: wave w takes hidden block nt = w % NT and the
 //             K-chunks kc = w / NT + (16 / NT) i; the corrupted copy only
 //             differs in block c, so z~ = z - zctr + zcor (§1 model, x~);
@@ -27,15 +27,11 @@
 // two workgroups take the same tile, both run the forward and the epilogue,
 // and each computes half of the dW1 and G output tiles, writing its own
 // dense-partial slot.
-// Three forms (FORM): 0, tiles one after another, three barriers each (a
-// workgroup with one tile); 1, tiles software-pipelined, two barriers each,
-// dW1 and G of one tile sharing a phase with the forward of the next; 2,
-// tiles in pairs, four barriers per pair: each phase holds the work of both
-// tiles (two independent MFMA chains per wave, and every wave busy in the
-// epilogue), at the price of a single X buffer.
+// TP is the tiles of a phase: 1 where a workgroup has a single tile, three
+// barriers; 2 where it has more, tiles in pairs, four barriers per pair: each
+// phase holds the work of both tiles (two independent MFMA chains per wave, and
+// every wave busy in the epilogue), at the price of a single X buffer.
 #pragma once
-#include <type_traits>
-
 #include "common.h"
 #include "launch.h"
 
@@ -64,22 +60,20 @@ struct F8Shape {
   static constexpr int XF4 = TP * XF1;              // ... per group of TP tiles
   static constexpr int XPT = (XF4 + kF8Threads - 1) / kF8Threads;  // pieces per thread
   static constexpr int S = K + 4;            // W1 row stride in LDS
-  static constexpr int NXB = TP == 1 ? 2 : 1;  // X buffers
   // LDS, in floats
   static constexpr int kW1 = HP * S;
-  static constexpr int kX = XF4 * 4;                       // one X buffer
+  static constexpr int kX = XF4 * 4;                       // X
   static constexpr int kZp = kF8Waves * 3 * 4 * kWave;     // forward split-K partials
   static constexpr int kVt = TP * 3 * kTileRows * (HP + 1);
   static constexpr int kRed = kF8Waves * (2 * HP + 2);
-  static constexpr int kLds = kW1 + NXB * kX + kZp + kVt + kRed;
+  static constexpr int kLds = kW1 + kX + kZp + kVt + kRed;
   static_assert(D % 16 == 0 && WIN % 2 == 1 && kF8Waves % (TP * NT) == 0, "shape");
   static_assert(kLds * 4 <= 160 * 1024, "LDS of one workgroup");
   static_assert(HP <= 32, "one hidden unit per lane of each 32-lane row half");
 };
 
-template <int D, int WIN, int NT, int FORM, int NH>
+template <int D, int WIN, int NT, int TP, int NH>
 __device__ void fwdbwd8_wg(const FwdArgs& a, int wg, float* lds) {
-  constexpr int TP = FORM == 2 ? 2 : 1;  // tiles per phase
   using Sh = F8Shape<D, WIN, NT, TP>;
   constexpr int HP = Sh::HP, K = Sh::K, C = Sh::C, W1P = Sh::W1P, DQ = Sh::DQ, QD = Sh::QD;
   constexpr int NCH = Sh::NCH, CPW = Sh::CPW, NGT = Sh::NGT, GPW = Sh::GPW;
@@ -94,8 +88,8 @@ __device__ void fwdbwd8_wg(const FwdArgs& a, int wg, float* lds) {
   const int tpf = otf / NT, ntf = otf % NT;
 
   float* w1s = lds;                       // [HP][K+4]
-  float* xl = w1s + Sh::kW1;              // [NXB][TP][W1P][QD][16] float4
-  float* zp = xl + Sh::NXB * Sh::kX;      // [kqf][3][otf][4][64]
+  float* xl = w1s + Sh::kW1;              // [TP][W1P][QD][16] float4
+  float* zp = xl + Sh::kX;                // [kqf][3][otf][4][64]
   float* vt = zp + Sh::kZp;               // [TP][3][16][HP+1]
   float* red = vt + Sh::kVt;              // [waves][2*HP+2]
 
@@ -104,7 +98,7 @@ __device__ void fwdbwd8_wg(const FwdArgs& a, int wg, float* lds) {
   // every second dW1 output tile and every second G output tile (linear
   // indices L = 2 (w + 16 i) + h); each writes its own partial slot, and the
   // db1 / dw2 / loss sums come from half 0 only.
-  static_assert(NH == 1 || (NH == 2 && FORM == 0), "the split takes single-tile workgroups");
+  static_assert(NH == 1 || (NH == 2 && TP == 1), "the split takes single-tile workgroups");
   constexpr int nh = NH;
   const int h = wg & (nh - 1);
   const int tile0 = (wg / nh) * a.tiles_per_wg;
@@ -145,19 +139,19 @@ __device__ void fwdbwd8_wg(const FwdArgs& a, int wg, float* lds) {
     }
     if (bad) atomicOr(a.flag, kFlagBadId);
   };
-  auto store_x = [&](int buf, const f4 (&xr)[XPT]) {
+  auto store_x = [&](const f4 (&xr)[XPT]) {
 #pragma unroll
     for (int p = 0; p < XPT; ++p) {
       const int pi = t + kF8Threads * p;
-      if (pi < XF4) st4(xl + buf * Sh::kX + 4 * pi, xr[p]);
+      if (pi < XF4) st4(xl + 4 * pi, xr[p]);
     }
   };
   // ---- prologue: ids of the first tile, W1 and the first tile's rows in
   // flight together (the rows wait only for the ids), then the ids of the
-  // second tile
-  int32_t ids[2][XPT];
+  // second pair
+  int32_t ids[XPT], idn[XPT];
   f4 xr[XPT];
-  load_ids(tile0, ids[0]);
+  load_ids(tile0, ids);
   {  // W1 into LDS (rows >= H zero); loads batched before the stores
     constexpr int N4 = HP * (K / 4);
     constexpr int U = (N4 + kF8Threads - 1) / kF8Threads;
@@ -168,8 +162,8 @@ __device__ void fwdbwd8_wg(const FwdArgs& a, int wg, float* lds) {
       const int n = i / (K / 4), k4 = i - n * (K / 4);
       v[u] = (i < N4 && n < a.H) ? ld4(a.W1 + (size_t)n * K + 4 * k4) : kZero4;
     }
-    load_x(ids[0], xr);
-    if (ntl > TP) load_ids(tile0 + TP, ids[1]);
+    load_x(ids, xr);
+    if (TP == 2 && ntl > TP) load_ids(tile0 + TP, idn);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = u * kF8Threads + t;
@@ -334,43 +328,28 @@ __device__ void fwdbwd8_wg(const FwdArgs& a, int wg, float* lds) {
     }
   };
 
-  if constexpr (FORM == 0) {
-    // Tiles one after another, three barriers each (X staged, forward
-    // partials, V).  Used when a workgroup has a single tile: the pipelined
-    // form measured 0.3 us slower there.
-    for (int tt = 0; tt < ntl; ++tt) {
-      const int tile = tile0 + tt;
-      const int buf = tt & 1;
-      const float* X = xl + buf * Sh::kX;
-      store_x(buf, xr);
-      __syncthreads();  // X of this tile (and W1) staged
-      if (tt + 1 < ntl) {
-        load_x(ids[(tt + 1) & 1], xr);                      // rows of the next tile
-        if (tt + 2 < ntl) load_ids(tile + 2, ids[tt & 1]);  // ids two tiles ahead
-      }
-      forward(X);
-      __syncthreads();  // forward partials written
-      epilogue(tile * kTileRows);
-      __syncthreads();  // V written
-      backward(X, tile * kTileRows);
-    }
-  } else if constexpr (FORM == 2) {
+  if constexpr (TP == 1) {
+    store_x(xr);
+    __syncthreads();  // X (and W1) staged
+    forward(xl);
+    __syncthreads();  // forward partials written
+    epilogue(tile0 * kTileRows);
+    __syncthreads();  // V written
+    backward(xl, tile0 * kTileRows);
+  } else {
     // Pairs of tiles, four barriers per pair (X staged, forward partials, V,
     // and the end of the pair's dW1 before the next pair's rows overwrite
-    // the single X buffer).  tiles_per_wg is even, so the second tile of a
-    // pair is this workgroup's, or past the last tile (rows >= B).
+    // X).  tiles_per_wg is even, so the second tile of a pair is this
+    // workgroup's, or past the last tile (rows >= B).
     // The next pair's ids take one set of registers: their rows are addressed
-    // before the ids of the pair after it replace them.  (ids[(gi + 1) & 1] and
-    // ids[gi & 1], indexed by the loop's counter, came out of the compiler with one
-    // condition for both writes: an odd gi wrote neither, and every second pair from
-    // the fourth on read row 0.)
+    // before the ids of the pair after it replace them.  (Two sets indexed by the
+    // loop's counter came out of the compiler with one condition for both
+    // writes: an odd gi wrote neither, and every second pair from the fourth on
+    // read row 0.)
     const int ng = (ntl + 1) / 2;
-    int32_t idn[XPT];
-#pragma unroll
-    for (int p = 0; p < XPT; ++p) idn[p] = ids[1][p];
     for (int gi = 0; gi < ng; ++gi) {
       const int row0 = (tile0 + 2 * gi) * kTileRows;
-      store_x(0, xr);
+      store_x(xr);
       __syncthreads();  // X of this pair (and W1) staged
       if (gi + 1 < ng) {
         load_x(idn, xr);                                         // rows of the next pair
@@ -382,38 +361,6 @@ __device__ void fwdbwd8_wg(const FwdArgs& a, int wg, float* lds) {
       __syncthreads();  // V written
       backward(xl, row0);
       if (gi + 1 < ng) __syncthreads();  // X and vt free (uniform branch)
-    }
-  } else {
-    // Software pipeline, two barriers per tile: the epilogue of tile t runs
-    // beside the staging of tile t+1's rows (into the other X buffer), then
-    // dW1 and G of tile t run in one phase with the forward of tile t+1.
-    // Between a buffer's last reader and its next writer there is always a
-    // barrier: zp (forward t+1 after the epilogue of t), vt (epilogue t+1
-    // after dW1/G of t), X[t&1] (rows of t+2 after dW1 of t).
-    store_x(0, xr);
-    if (ntl > 1) {
-      load_x(ids[1], xr);                                  // rows of tile 1
-      if (ntl > 2) load_ids(tile0 + 2, ids[0]);            // ids of tile 2
-    }
-    __syncthreads();  // X of tile 0 and W1 staged
-    forward(xl);
-    __syncthreads();  // forward partials of tile 0 written
-    for (int tt = 0; tt < ntl; ++tt) {
-      const int row0 = (tile0 + tt) * kTileRows;
-      epilogue(row0);
-      if (tt + 1 < ntl) {
-        store_x((tt + 1) & 1, xr);                         // rows of tile tt+1
-        if (tt + 2 < ntl) {
-          load_x(ids[tt & 1], xr);                         // rows of tile tt+2
-          if (tt + 3 < ntl) load_ids(tile0 + tt + 3, ids[(tt + 1) & 1]);
-        }
-      }
-      __syncthreads();  // V of tile tt and X of tile tt+1 written
-      backward(xl + (tt & 1) * Sh::kX, row0);
-      if (tt + 1 < ntl) {  // (uniform: every wave takes the same branch)
-        forward(xl + ((tt + 1) & 1) * Sh::kX);
-        __syncthreads();  // forward partials of tile tt+1 written; vt, X[tt&1] free
-      }
     }
   }
 

@@ -35,16 +35,14 @@ __device__ __forceinline__ f4 mfma16(float a, float b, f4 c) {
 // = 24 tiles of window 5, d 64 in one pass of the four waves.
 constexpr int kGTiles = 6;
 
-// D_ and WIN_ fix the embedding width and the window at compile time for
-// the common shapes (0: taken from the arguments).
-template <int NT, int CPW, int D_, int WIN_>
+template <int NT, int CPW>
 __device__ void fwdbwd_wg(const FwdArgs& a, int wg, float* lds) {
   constexpr int HP = NT * 16;
   const int t = threadIdx.x, lane = t & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(t / kWave);  // wave-uniform: scalar branches
   const int n16 = lane & 15, g = lane >> 4;
-  const int d = D_ ? D_ : a.d;
-  const int win = WIN_ ? WIN_ : a.win;
+  const int d = a.d;
+  const int win = a.win;
   const int K = d * win;
   const int cc = win / 2;
   const int W1p = win + 1;

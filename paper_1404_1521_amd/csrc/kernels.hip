@@ -47,9 +47,7 @@
 namespace pg {
 
 // Two workgroups per CU when the shape's registers allow it without spills.
-// D and WIN (0: runtime) fix the embedding width and window of the common
-// shapes at compile time.
-template <int NT, int CPW, int D, int WIN>
+template <int NT, int CPW>
 __global__ __launch_bounds__(kBlock, (NT == 1 || (NT == 2 && CPW <= 5)) ? 2 : 1) void k_step_fwdbwd(FwdArgs a) {
   extern __shared__ float lds_f[];
   if ((int)blockIdx.x < a.n_sort) {  // small batches: the step's sort, partition blockIdx.x
@@ -59,14 +57,13 @@ __global__ __launch_bounds__(kBlock, (NT == 1 || (NT == 2 && CPW <= 5)) ? 2 : 1)
                       reinterpret_cast<uint32_t*>(lds_f));
     return;
   }
-  fwdbwd_wg<NT, CPW, D, WIN>(a, blockIdx.x - a.n_sort, lds_f);
+  fwdbwd_wg<NT, CPW>(a, blockIdx.x - a.n_sort, lds_f);
 }
 
 // The same step for the compile-time shapes, 16 waves per workgroup (the
-// sort role of small batches too); FORM: 0 single tile, 1 pipelined tiles, 2
-// tile pairs; NH = 2: two workgroups per tile, each taking half of the
-// backward.
-template <int D, int WIN, int NT, int FORM, int NH>
+// sort role of small batches too); TP: 1 a single tile, 2 tile pairs; NH = 2:
+// two workgroups per tile, each taking half of the backward.
+template <int D, int WIN, int NT, int TP, int NH>
 __global__ __launch_bounds__(kF8Threads, 1) void k_step_fwdbwd8(FwdArgs a) {
   extern __shared__ float lds_f[];
   if ((int)blockIdx.x < a.n_sort) {
@@ -76,7 +73,7 @@ __global__ __launch_bounds__(kF8Threads, 1) void k_step_fwdbwd8(FwdArgs a) {
                           reinterpret_cast<uint32_t*>(lds_f));
     return;
   }
-  fwdbwd8_wg<D, WIN, NT, FORM, NH>(a, blockIdx.x - a.n_sort, lds_f);
+  fwdbwd8_wg<D, WIN, NT, TP, NH>(a, blockIdx.x - a.n_sort, lds_f);
 }
 
 // The split form of the d 64 shape (large batches: never with the sort role).
@@ -164,9 +161,9 @@ static hipError_t launch_sort(const KeyFn& kf, int N, const SortPlan& plan, cons
 template <int NT>
 static hipError_t launch_fwdbwd_nt(const FwdArgs& a, int cpw, int grid, size_t lds,
                                    const Launch& L) {
-  if (cpw <= 2) return pg_launch(k_step_fwdbwd<NT, 2, 0, 0>, dim3(grid), dim3(kBlock), lds, L, a);
-  if (cpw <= 5) return pg_launch(k_step_fwdbwd<NT, 5, 0, 0>, dim3(grid), dim3(kBlock), lds, L, a);
-  return pg_launch(k_step_fwdbwd<NT, 8, 0, 0>, dim3(grid), dim3(kBlock), lds, L, a);
+  if (cpw <= 2) return pg_launch(k_step_fwdbwd<NT, 2>, dim3(grid), dim3(kBlock), lds, L, a);
+  if (cpw <= 5) return pg_launch(k_step_fwdbwd<NT, 5>, dim3(grid), dim3(kBlock), lds, L, a);
+  return pg_launch(k_step_fwdbwd<NT, 8>, dim3(grid), dim3(kBlock), lds, L, a);
 }
 
 int fwdbwd8_shape(int d, int win, int NT) {
@@ -176,22 +173,20 @@ int fwdbwd8_shape(int d, int win, int NT) {
 }
 
 size_t fwdbwd8_lds_bytes(int shape, int tiles_per_wg) {
-  constexpr int TP = kF8MultiForm == 2 ? 2 : 1;  // tiles per phase of the multi-tile form
-  if (tiles_per_wg > 1) return F8Shape<16, 5, 1, TP>::kLds * sizeof(float);
+  if (tiles_per_wg > 1) return F8Shape<16, 5, 1, 2>::kLds * sizeof(float);
   return (shape == 1 ? F8Shape<64, 5, 2, 1>::kLds : F8Shape<16, 5, 1, 1>::kLds) * sizeof(float);
 }
 
 hipError_t launch_step_fwdbwd8(const FwdArgs& a, int shape, int grid, size_t lds,
                                const Launch& L) {
   const dim3 g(grid), b(kF8Threads);
-  constexpr int MF = kF8MultiForm;
   // (the d 64 shape has one tile per workgroup: larger batches take the split form)
   static_assert(kFsMinBatch <= kF8MaxWorkgroups * kTileRows + 1, "one tile per workgroup");
   if (shape == 1)
-    return a.split == 2 ? pg_launch(k_step_fwdbwd8<64, 5, 2, 0, 2>, g, b, lds, L, a)
-                        : pg_launch(k_step_fwdbwd8<64, 5, 2, 0, 1>, g, b, lds, L, a);
-  return a.tiles_per_wg > 1 ? pg_launch(k_step_fwdbwd8<16, 5, 1, MF, 1>, g, b, lds, L, a)
-                            : pg_launch(k_step_fwdbwd8<16, 5, 1, 0, 1>, g, b, lds, L, a);
+    return a.split == 2 ? pg_launch(k_step_fwdbwd8<64, 5, 2, 1, 2>, g, b, lds, L, a)
+                        : pg_launch(k_step_fwdbwd8<64, 5, 2, 1, 1>, g, b, lds, L, a);
+  return a.tiles_per_wg > 1 ? pg_launch(k_step_fwdbwd8<16, 5, 1, 2, 1>, g, b, lds, L, a)
+                            : pg_launch(k_step_fwdbwd8<16, 5, 1, 1, 1>, g, b, lds, L, a);
 }
 
 hipError_t launch_step_split(const FwdArgs& a, int grid, const Launch& L) {

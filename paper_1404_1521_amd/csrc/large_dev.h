@@ -782,7 +782,6 @@ __global__ __launch_bounds__(CG * PG * kWave) void k_large_g(LargeArgs a) {
   store();
   __syncthreads();
   int ty = type_of(o_lo);
-  const int ty_last = type_of(o_hi - 1);
   while (o >= 0) {
     if (type_of(o) != ty) {  // every wave reaches a new type at the same position
       __syncthreads();
