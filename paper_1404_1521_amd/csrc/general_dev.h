@@ -97,7 +97,8 @@ struct GenArgsP : GenArgs<T> {
   static constexpr bool kPacked = true;
 };
 
-template <bool STREAM, class T>
+// (entries' rows of these formats are read plainly whatever the list's length)
+template <bool, class T>
 __device__ __forceinline__ float seg_load(const GenArgs<T>& a, size_t i) {
   return Elem<T>::get(a.Y[i]);
 }
@@ -190,7 +191,7 @@ __device__ __forceinline__ uint32_t pack2(float x, float y) {
   return (uint32_t)Elem<T>::put(x).bits | ((uint32_t)Elem<T>::put(y).bits << 16);
 }
 
-template <int CH, bool STREAM, class A>
+template <int CH, class A>
 __device__ void seg_walk_packed(const A& a, const ChunkInfo& ci, uint64_t tails, uint64_t complete,
                                 int first_tail, bool starts_long, const ChunkSink& sink) {
   using T = typename A::elem;
@@ -333,8 +334,8 @@ __device__ __forceinline__ void seg_add4(const GenArgs<T>& a, size_t i, int n, f
   seg_put4(a, i, n, seg_row4(a, i, n) + v);
 }
 
-// Assignment over a sorted list (long ones): one wave per 64 sorted entries; an entry whose successor has
-// another key (or that is the last) ends its row's segment, so it is the
+// Assignment over a sorted list (long ones): one wave per 64 sorted entries; an
+// entry whose successor has another key (or that is the last) ends its row's segment, so it is the
 // row's last entry in index order, and its Y row is copied.  The error words
 // are read beside the keys.  Each such entry's (entry, row) goes to the
 // wave's LDS slots by its rank among them, and the rows are copied as words
@@ -406,8 +407,8 @@ __global__ __launch_bounds__(kBlock) void k_gen_set(GenArgs<T> a, int n_e) {
 // back), so `last` is all zero between calls, whatever they did.
 //
 // What bounds the marking is its atomics: about 10 ns each on the word of one
-// frequent row, about 4 per ns over many rows (327,680 entries: 50 us, where
-// the sort takes 21).  So a workgroup first drops all but the last entry of a
+// frequent row, about 0.25 ns each over many rows (beside the 16-18 us of a sort,
+// whatever the list's length: kSetMarkN).  So a workgroup first drops all but the last entry of a
 // repeated row: rows compete for slot row % kSetSlots of a table (the last
 // writer holds it), the holder's entries compete in LDS and one of them goes
 // to memory; entries whose row lost its slot go to memory themselves.

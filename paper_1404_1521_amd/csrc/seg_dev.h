@@ -133,7 +133,8 @@ struct ChunkSink {
 // a completed piece is added with one float atomic per element at the L2
 // (none by lanes past the row end).
 //
-// Entries' rows are read once: with STREAM past the caches' replacement order,
+// Entries' rows are read once: float32 ones with STREAM past the caches' replacement
+// order (the 16-bit formats and their kernels' float32 rows plainly),
 // which keeps the table rows and the sort's lists there (the range-wise apply
 // of long lists: B = 65,536 135 -> 127.5 us per step, B = 5003 38.3 -> 37.7,
 // wide layers 310 -> 307, the 327,680-row scatter-add 47.6 -> 47.3).  The
@@ -159,7 +160,7 @@ __device__ __forceinline__ void seg_close(const SegArgs& a, size_t i, float v) {
 
 // The walk of argument sets whose rows are 16-bit elements read and written
 // two rows per 32-bit word (kPacked; defined with those formats).
-template <int CH, bool STREAM, class A>
+template <int CH, class A>
 __device__ void seg_walk_packed(const A& a, const ChunkInfo& ci, uint64_t tails, uint64_t complete,
                                 int first_tail, bool starts_long, const ChunkSink& sink);
 
@@ -197,7 +198,7 @@ __device__ bool seg_apply_rows(const A& a, int i0, int end, const ChunkSink& sin
     sink.meta[4] = ci.last_key;
   }
   if constexpr (A::kPacked) {
-    seg_walk_packed<CH, STREAM>(a, ci, tails, complete, first_tail, starts_long, sink);
+    seg_walk_packed<CH>(a, ci, tails, complete, first_tail, starts_long, sink);
     return true;
   }
   // One block of 64 columns.  Every lane walks, so that every test below is a
