@@ -27,6 +27,7 @@ if ROOT not in sys.path:
 COUNTERS = os.path.join(ROOT, "profiles", "hbm_counters_{}.md")
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 F32_MATRIX_PEAK_TFLOPS = 157.3  # MI355X dense fp32 MFMA, published
+SPLIT_MATRIX_PEAK_TFLOPS = 2500.0 / 6  # dense bfloat16 MFMA, six products per float32 one
 F32_VECTOR_PEAK_TFLOPS = 157.3  # 256 CU x 4 SIMD x 64 lanes x 2 flop (FMA) x 2.4 GHz
 
 
@@ -64,17 +65,18 @@ def parse():
 # Algorithmic bytes and flops of each kernel, from the batch itself.
 
 def _hp(H):
-    return -(-H // 16) * 16
+    return 16 if H <= 16 else (32 if H <= 32 else 64)
 
 
-def seg_chunk(N):
-    """Sorted entries per wave in the segmented update (mirrors the library's choice)."""
-    return 16 if N <= 131072 else 64
+def seg_range(N):
+    """Sorted entries per range of the segmented update: four waves' chunks
+    (mirrors the library's choice)."""
+    return 4 * (16 if N <= 16384 or 65536 < N <= 131072 else 32)
 
 
-def batch_structure(wins, cors, ch):
-    """Distinct rows U, rows whose sorted entries span several chunks, and the
-    chunk partials those rows leave (entry order = window-major, corrupt last)."""
+def batch_structure(wins, cors, rg):
+    """Distinct rows U, rows whose sorted entries span several ranges, and the
+    range partials those rows leave (entry order = window-major, corrupt last)."""
     import numpy as np
     B, win = wins.shape
     keys = np.concatenate([wins, cors[:, None]], axis=1).ravel()
@@ -82,20 +84,52 @@ def batch_structure(wins, cors, ch):
     sk = keys[order]
     heads = np.flatnonzero(np.r_[True, sk[1:] != sk[:-1]])
     ends = np.r_[heads[1:], sk.size]
-    cs, ce = heads // ch, (ends - 1) // ch
+    cs, ce = heads // rg, (ends - 1) // rg
     long_rows = cs != ce
     return {"U": int(heads.size), "long_rows": int(long_rows.sum()),
             "partials": int((ce - cs + 1)[long_rows].sum())}
 
 
-def step_model(w, B, st, passes, n_parts):
+def split_tiles(w, B):
+    """Whether the fused step runs in 32-window tiles on split operands
+    (kFsMinBatch of launch.h)."""
+    return (w.d, w.win) == (64, 5) and 16 < w.H <= 32 and B >= 3585
+
+
+def dense_parts(w, B):
+    """(dW1 partials, db1/dw2/loss partials, columns of a dW1 partial) that a step
+    writes: the tiling of api.hip and launch.h."""
+    def ceil(a, b):
+        return -(-a // b)
+    if w.H > 64:
+        cols = 128 if w.d % 128 == 0 else 64
+        ncol = (w.win + 1) * w.d // cols
+        lds = 2 * 32 * 6 * (w.H + cols) + 2048 * 4
+        fit = 2 if 2 * lds <= 160 * 1024 else 1
+        steps = ceil(B, 32)
+        n = max(1, min(fit * 256 // ncol, steps))
+        slices = ceil(B, min(ceil(steps, n) * 32, 2048))
+        mt = 1 if B <= 16 * 256 else (2 if B <= 32 * 256 or w.H == 192 else 4)
+        return slices, ceil(B, 16 * mt), w.K + w.d
+    rows = 32 if split_tiles(w, B) else 16
+    pairs = (w.d, w.win) == (16, 5) and w.H <= 16
+    most = 256 if rows == 32 or pairs or ((w.d, w.win) == (64, 5) and 16 < w.H <= 32) else 512
+    tiles = ceil(B, rows)
+    per = ceil(tiles, min(most, tiles))
+    if pairs and per > 1:
+        per += per & 1
+    n = ceil(tiles, per)
+    return n, n, w.K
+
+
+def step_model(w, B, st, passes):
     """({kernel: (bytes, flops, engine)}, {kernel: overhead bytes}) of one step.
 
     The first map holds the method's own bytes and flops per step: what the
     operation must read, write and compute whatever the implementation.  The
     second holds the traffic this implementation adds on top (the dense
-    gradient partials that one kernel writes and the next reads back), which
-    is reported beside the roofline, never inside it.
+    gradient partials that one kernel writes and the next reads back, W1's
+    fragments), which is reported beside the roofline, never inside it.
 
     Hidden layers of at most 64 units (one fused kernel):
     fwdbwd: ids + every window row and corrupt row read once (the gather),
@@ -106,56 +140,60 @@ def step_model(w, B, st, passes, n_parts):
       elementwise work, not counted).  Overhead: the dense partial slots.
     Wider layers (three contractions):
     fwdbwd: ids and rows read, W1 read, the per-window vectors (3H floats)
-      and the db1/dw2/loss partials written; flops 2HK + 2Hd per window.
-    wide_dw1: ids and rows read, the per-window vectors read, one dW1
-      partial per 1024 windows written (the kernel sizes its slices by the
-      batch); flops 2HK + 2Hd per window.
+      written; flops 2HK + 2Hd per window.  Overhead: W1's fragments in two
+      layouts of 6 B a weight written and one read, the db1/dw2/loss partials.
+    wide_dw1: ids and rows read, the per-window vectors read, dW1 written;
+      flops 2HK + 2Hd per window.  Overhead: its slices, H (K + d) floats each.
     wide_g: the per-window vectors and W1 read, G written; flops
-      (win+1) 2Hd per window.
+      (win+1) 2Hd per window.  Overhead: fragments of 6 B a weight for 4.
     sort: 16 B per entry per radix pass (keys and values, read and written).
     update: sorted keys+values and every G row read once, every distinct row
       of E read and written, W1/b1/w2/b2 read and written; flops = one add
       per G element.  Overhead: the dense partials read back.
-    segfix: the chunk partials of long rows (d floats each) read, their rows
+    segfix: the range partials of long rows (d floats each) read, their rows
       read and written.
+
+    Engines: "mfma" the float32 matrix instructions; "mfma_split" the bfloat16
+    ones at six products per float32 product (wide layers, 32-window tiles).
     """
     d, win, H, K = w.d, w.win, w.H, w.K
     N = B * (win + 1)
     dense = (H * K + 2 * H + 1) * 4
     rows_in = B * ((win + 1) * 4 + (win + 1) * d * 4)
     g_out = B * (win + 1) * d * 4
+    n_parts, n_vparts, cols = dense_parts(w, B)
     if H > 64:
-        slices = -(-B // 1024)
-        vparts = -(-B // 32)
         vec = B * 3 * H * 4
-        part_bytes = slices * H * K * 4 + vparts * (2 * H + 2) * 4
+        dw1_parts, vec_parts = n_parts * H * cols * 4, n_vparts * (2 * H + 2) * 4
+        part_bytes = dw1_parts + vec_parts
         m = {
-            "fwdbwd": (rows_in + H * K * 4 + vec + vparts * (2 * H + 2) * 4,
-                       B * (2 * H * K + 2 * H * d), "mfma"),
-            "wide_dw1": (rows_in + vec + slices * H * K * 4, B * (2 * H * K + 2 * H * d), "mfma"),
-            "wide_g": (vec + H * K * 4 + g_out, B * (win + 1) * 2 * H * d, "mfma"),
+            "fwdbwd": (rows_in + H * K * 4 + vec, B * (2 * H * K + 2 * H * d), "mfma_split"),
+            "wide_dw1": (rows_in + vec + H * K * 4, B * (2 * H * K + 2 * H * d), "mfma_split"),
+            "wide_g": (vec + H * K * 4 + g_out, B * (win + 1) * 2 * H * d, "mfma_split"),
         }
+        over = {"fwdbwd": H * K * (12 + 6) + vec_parts, "wide_dw1": dw1_parts - H * K * 4,
+                "wide_g": H * K * 2}
     else:
         Hp = _hp(H)
-        part_stride = Hp * K + 2 * Hp + 2
-        part_bytes = n_parts * part_stride * 4
+        part_bytes = n_parts * (Hp * K + 2 * Hp + 2) * 4
         m = {
             "fwdbwd": (rows_in + g_out + H * K * 4,
-                       B * (4 * H * K + 4 * H * d + (win + 1) * 2 * H * d), "mfma"),
+                       B * (4 * H * K + 4 * H * d + (win + 1) * 2 * H * d),
+                       "mfma_split" if split_tiles(w, B) else "mfma"),
         }
+        over = {"fwdbwd": part_bytes}
     m["sort"] = (N * 16 * passes, 0, "hbm")
     m["update"] = (N * (8 + d * 4) + 2 * st["U"] * d * 4 + 2 * dense, N * d, "alu")
     m["segfix"] = (st["partials"] * d * 4 + 2 * st["long_rows"] * d * 4, st["partials"] * d, "alu")
-    over = {"fwdbwd": part_bytes, "update": part_bytes}
-    if H > 64:
-        over = {"wide_dw1": slices * H * K * 4, "update": part_bytes}
+    over["update"] = part_bytes
     return m, over
 
 
 def roofline(nbytes, nflops, engine, ms):
     """Bound by intensity against the ridge of the kernel's own engine."""
     sec = ms * 1e-3
-    peak_f = F32_MATRIX_PEAK_TFLOPS if engine == "mfma" else F32_VECTOR_PEAK_TFLOPS
+    peak_f = {"mfma": F32_MATRIX_PEAK_TFLOPS, "mfma_split": SPLIT_MATRIX_PEAK_TFLOPS}.get(
+        engine, F32_VECTOR_PEAK_TFLOPS)
     ridge = peak_f * 1e12 / (HBM_PEAK_GBS * 1e9)
     if nflops and nbytes and nflops / nbytes > ridge:
         ach = nflops / sec / 1e12
@@ -587,15 +625,11 @@ def main():
 
     # structure of the timed batches (sampled) for the byte model
     small = N <= 8192 and w.H <= 64
-    samp = [batch_structure(wins[s], cors[s], seg_chunk(N)) for s in range(Wm + K, Wm + K + min(K, 8))]
+    samp = [batch_structure(wins[s], cors[s], seg_range(N)) for s in range(Wm + K, Wm + K + min(K, 8))]
     st = {k: float(np.mean([x[k] for x in samp])) for k in samp[0]}
     key_bits = max(1, int(w.V - 1).bit_length())
     passes = 0 if small else -(-key_bits // 9)
-    # dense-partial slots: one per workgroup of the fused kernel (256 at most
-    # for the compile-time shapes d 64 / d 16 with window 5, 512 otherwise)
-    nt = -(-w.H // 16)
-    n_parts = min(-(-B // 16), 256 if (w.d, w.win, nt) in ((64, 5, 2), (16, 5, 1)) else 512)
-    model, overhead = step_model(w, B, st, passes, n_parts)
+    model, overhead = step_model(w, B, st, passes)
     model_flops = sum(v[1] for v in model.values())
     per = {k: (v[0] / v[1], v[1] / K) for k, v in kt.items() if v[1]}
     step_us = {k: v[0] * v[1] for k, v in per.items()}

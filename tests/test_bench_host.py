@@ -7,6 +7,7 @@ import subprocess
 import sys
 
 import bench
+import workloads
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -45,6 +46,24 @@ def test_counter_traffic_calibrates_and_rejects_stale_summaries(tmp_path, monkey
     data["source_sha256"] = "0" * 64
     (tmp_path / "hbm_counters_x.md").write_text("```json\n" + json.dumps(data) + "\n```\n")
     assert bench.counter_traffic("x", "fwdbwd") is None
+
+
+def test_model_counts_the_kernels_partials():
+    """The partials of the dense gradients that the byte model prices: 21 slices
+    of K + d columns for the wide preset (12 blocks of 128 columns on 256 CUs),
+    32-window tiles for d 64 from 3,585 windows on, pairs of 16-window tiles for
+    d 16, single ones below."""
+    stress = workloads.PRESETS["stress"]
+    assert bench.dense_parts(stress, stress.B) == (21, 256, stress.K + stress.d)
+    poly, tiny = workloads.PRESETS["sweep_1024"], workloads.PRESETS["tiny"]
+    for w, B, n in ((poly, 1024, 64), (poly, 3584, 224), (poly, 3585, 113), (poly, 5003, 157),
+                    (poly, 65_536, 256), (tiny, 4096, 256), (tiny, 4097, 129), (tiny, 24_577, 193)):
+        assert bench.dense_parts(w, B) == (n, n, w.K), (w.name, B)
+    st = {"U": 1.0, "partials": 0.0, "long_rows": 0.0}
+    m, over = bench.step_model(stress, stress.B, st, 2)
+    assert over["wide_dw1"] == (21 * (stress.K + stress.d) - stress.K) * stress.H * 4
+    assert m["wide_dw1"][2] == "mfma_split" and bench.step_model(poly, 1024, st, 0)[0]["fwdbwd"][2] == "mfma"
+    assert bench.step_model(poly, 1024, st, 0)[0]["fwdbwd"][0] == 1024 * 3096 + poly.H * poly.K * 4
 
 
 def test_more_than_one_gpu_is_refused():
