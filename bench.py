@@ -93,7 +93,7 @@ def batch_structure(wins, cors, rg):
 def split_tiles(w, B):
     """Whether the fused step runs in 32-window tiles on split operands
     (kFsMinBatch of launch.h)."""
-    return (w.d, w.win) == (64, 5) and 16 < w.H <= 32 and B >= 3585
+    return (w.d, w.win) == (64, 5) and 16 < w.H <= 32 and B >= 3745
 
 
 def dense_parts(w, B):

@@ -221,14 +221,15 @@ constexpr int kF8Waves = 16;
 constexpr int kF8Threads = kF8Waves * kWave;  // 1024
 constexpr int kF8MaxWorkgroups = 256;         // one workgroup per CU
 // The split form of the d 64 shape (fwdbwd_split_dev.h): 32-window tiles, from
-// this batch on.  Below, its tiles leave most CUs idle and its preparation of
-// W1 weighs more than the tile.  Steps (same box, alternating), float32 tiles
-// against split ones: B = 2048 29.7 against 32.5 us, 3000 33.0, 33.9; 3500
-// 34.4, 34.4; 4096 37.1, 35.6; 8192 44.5, 42.0; 16,384 62.8, 55.1; 32,768 86.9,
-// 75.4; 65,536 128.1, 109.6.
+// this batch on (the first above 117 tiles).  Below, its tiles leave most CUs idle
+// and its preparation of W1 weighs more than the tile.  Steps (same box,
+// alternating), float32 tiles against split ones: B = 2048 29.1 against 32.1 us,
+// 3000 33.1, 33.9; 3500 34.7, 35.0; 3700 35.3, 35.4; 4096 37.3, 36.3; and with two
+// and more float32 tiles per workgroup, in the form that did this until then: 8192
+// 44.5, 42.4; 16,384 62.8, 56.1; 32,768 86.9, 76.5; 65,536 128.1, 112.
 constexpr int kFsRows = 32;
 constexpr int kFsThreads = 8 * kWave;
-constexpr int kFsMinBatch = 3585;
+constexpr int kFsMinBatch = 3745;
 hipError_t launch_step_split(const FwdArgs& a, int grid, const Launch& L);
 hipError_t launch_step_fwdbwd8(const FwdArgs& a, int shape, int grid, size_t lds,
                                const Launch& L);

@@ -51,12 +51,12 @@ def test_counter_traffic_calibrates_and_rejects_stale_summaries(tmp_path, monkey
 def test_model_counts_the_kernels_partials():
     """The partials of the dense gradients that the byte model prices: 21 slices
     of K + d columns for the wide preset (12 blocks of 128 columns on 256 CUs),
-    32-window tiles for d 64 from 3,585 windows on, pairs of 16-window tiles for
+    32-window tiles for d 64 from 3,745 windows on, pairs of 16-window tiles for
     d 16, single ones below."""
     stress = workloads.PRESETS["stress"]
     assert bench.dense_parts(stress, stress.B) == (21, 256, stress.K + stress.d)
     poly, tiny = workloads.PRESETS["sweep_1024"], workloads.PRESETS["tiny"]
-    for w, B, n in ((poly, 1024, 64), (poly, 3584, 224), (poly, 3585, 113), (poly, 5003, 157),
+    for w, B, n in ((poly, 1024, 64), (poly, 3744, 234), (poly, 3745, 118), (poly, 5003, 157),
                     (poly, 65_536, 256), (tiny, 4096, 256), (tiny, 4097, 129), (tiny, 24_577, 193)):
         assert bench.dense_parts(w, B) == (n, n, w.K), (w.name, B)
     st = {"U": 1.0, "partials": 0.0, "long_rows": 0.0}

@@ -588,10 +588,10 @@ def test_tile_pairs_ragged(B, pairs, last, windows):
     run_both(w, 2, B, 0)
 
 
-# Both sides of the switch to 32-window tiles (3,585 windows), hidden layers that
+# Both sides of the switch to 32-window tiles (3,745 windows), hidden layers that
 # leave padding rows, a last tile of one window, the atomic update; and of the
 # switch of the d 16 shape to tile pairs (4,097 windows).
-@pytest.mark.parametrize("d,H,B,mode", [(64, 32, 3584, 0), (64, 32, 3585, 0), (64, 17, 3585, 1),
+@pytest.mark.parametrize("d,H,B,mode", [(64, 32, 3744, 0), (64, 32, 3745, 0), (64, 17, 3745, 1),
                                         (64, 25, 8193, 0), (64, 31, 16_417, 0), (16, 8, 4096, 0),
                                         (16, 16, 4097, 1)])
 def test_split_tiles_at_their_limits(d, H, B, mode):
@@ -693,7 +693,7 @@ def test_wide_scores_of_infinite_rows():
 # The kernels that split each float32 operand into three bfloat16 terms, against
 # 64 bits: inputs whose contractions can be read out of one call without a tanh
 # that matters, in shapes that take 32-window tiles (d 64, window 5, H 32, from
-# 3,585 windows on: one and eight tiles per workgroup) and the wide path (16, 32
+# 3,745 windows on: one and eight tiles per workgroup) and the wide path (16, 32
 # and 64 windows per forward workgroup).
 SPLIT_SHAPES = [(64, 5, 32, 4096), (64, 5, 32, 65_536), (128, 3, 128, 64), (192, 3, 192, 8192),
                 (256, 3, 256, 16_384)]
@@ -861,7 +861,7 @@ def test_split_infinite_gradient():
 
 # Batches that leave part of their last tile empty: 16 of a 32-window tile's
 # windows, 32 of a 64-window forward workgroup's, 9 of 16.
-@pytest.mark.parametrize("d,win,H,B", [(64, 5, 32, 3600), (128, 3, 128, 8224), (64, 3, 128, 23)])
+@pytest.mark.parametrize("d,win,H,B", [(64, 5, 32, 3760), (128, 3, 128, 8224), (64, 3, 128, 23)])
 def test_padding_windows_take_nothing_from_row_0(d, win, H, B):
     w = workloads.Workload("pad", V=300, d=d, win=win, H=H, B=B, lr=0.05, steps=1, zipf_s=1.0,
                            seed=28)
