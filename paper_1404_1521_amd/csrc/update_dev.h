@@ -81,17 +81,20 @@ __device__ void dense_sgd(const DenseArgs& a, int wg, int nwg, bool bad, float* 
         src += (size_t)n * a.kx;
         if ((unsigned)(k - a.c0) < (unsigned)a.kx) src2 = src + (a.K - a.c0);
       }
-      for (int p0 = g; p0 < np; p0 += 8 * SL) {
-        float v[8];
+      do {
+        for (int p0 = g; p0 < np; p0 += 8 * SL) {
+          float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int p = p0 + u * SL;
-          v[u] = p < np ? src[(size_t)p * stride] : 0.f;
-          if (src2 && p < np) v[u] += src2[(size_t)p * stride];
+          for (int u = 0; u < 8; ++u) {
+            const int p = p0 + u * SL;
+            v[u] = p < np ? src[(size_t)p * stride] : 0.f;
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) s += v[u];
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s += v[u];
-      }
+        src = src2;
+        src2 = nullptr;
+      } while (src);
     }
     red[t] = s;
     __syncthreads();
