@@ -137,7 +137,10 @@ struct ChunkSink {
 // order (the 16-bit formats and their kernels' float32 rows plainly),
 // which keeps the table rows and the sort's lists there (the range-wise apply
 // of long lists: B = 65,536 135 -> 127.5 us per step, B = 5003 38.3 -> 37.7,
-// wide layers 310 -> 307, the 327,680-row scatter-add 47.6 -> 47.3).  The
+// wide layers 310 -> 307, the 327,680-row scatter-add 47.6 -> 47.3; that one with
+// six sets of inputs in turn 55 -> 49, 140,000 rows of 256 74 -> 65, 500,000 of 100
+// 125 -> 131; only the same Y again and again, out of the caches, is slower so:
+// 47.2 -> 49.3).  The
 // partition-wise apply's rows (8,192 at most) were just written and still sit
 // in the L2: B = 1024 17.6 us plain, 17.7 streaming.
 template <bool STREAM, class T>
