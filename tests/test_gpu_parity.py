@@ -635,6 +635,15 @@ def test_other_shapes(w, mode):
     run_both(w, w.steps, w.B, mode)
 
 
+# The general fused kernel with several 16-window tiles per workgroup (above 8,192
+# windows): two and five of them, the last workgroup short, the last tile ragged.
+@pytest.mark.parametrize("d,win,H,B", [(64, 5, 64, 8200), (16, 3, 12, 33_001)])
+def test_general_kernel_several_tiles(d, win, H, B):
+    w = workloads.Workload(f"w{win}_d{d}_h{H}", V=20_000, d=d, win=win, H=H, B=B, lr=0.5, steps=2,
+                           zipf_s=1.0, seed=33)
+    run_both(w, 2, B)
+
+
 # Hidden layers wider than 64 units take the three-contraction path
 # (forward, dW1 slices, per-entry rows); B = 1030 crosses a 1024-window slice.
 LARGE_SHAPES = [
